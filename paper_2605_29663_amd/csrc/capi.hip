@@ -55,6 +55,69 @@ void* scratch_ptr(int device) {
 
 }  // namespace
 
+namespace {
+
+// Head of the bound table (FootTable) of a footprint given as in
+// set_footprint: a grid of about FOOT_CELLS square cells over the bounding
+// box and a margin of a quarter of the footprint's mean size, which keeps
+// most of the points next to the footprint on the grid, where the bounds are
+// closest.
+FootTable foot_head(int kind, const float* host, int count) {
+    const int w = kind == MPPI_FP_POLYGON ? 2 : 4;
+    std::vector<double> v(host, host + static_cast<size_t>(w) * count);
+    double lo[2] = {INFINITY, INFINITY}, hi[2] = {-INFINITY, -INFINITY}, reach = 0.0;
+    for (int b = 0; b < count; ++b)
+        for (int k = 0; k < 2; ++k) {
+            const double h = w == 4 ? v[4 * b + 2 + k] : 0.0;
+            lo[k] = std::min(lo[k], v[w * b + k] - h);
+            hi[k] = std::max(hi[k], v[w * b + k] + h);
+        }
+    const double W = hi[0] - lo[0], H = hi[1] - lo[1];
+    reach = std::hypot(std::max(std::fabs(lo[0]), std::fabs(hi[0])), std::max(std::fabs(lo[1]), std::fabs(hi[1])));
+    const double margin = 0.25 * std::sqrt(W * H) + 0.02 * (W + H);
+    const double w0 = W + 2 * margin, h0 = H + 2 * margin;
+    FootTable F{};
+    F.nx = std::max(8, std::min(FOOT_CELLS / 8, static_cast<int>(std::sqrt(FOOT_CELLS * w0 / h0))));
+    F.ny = FOOT_CELLS / F.nx;
+    const double dx = w0 / F.nx, dy = h0 / F.ny;
+    const double cx = 0.5 * (lo[0] + hi[0]), cy = 0.5 * (lo[1] + hi[1]);
+    const double d0 = w == 2 ? polygon_distance(v.data(), count, cx, cy) : cover_distance(v.data(), count, cx, cy);
+    F.cx = static_cast<float>(cx);
+    F.cy = static_cast<float>(cy);
+    // rounding of the single-precision geometry, far inside the search's slack
+    F.radius = static_cast<float>(0.5 * std::hypot(W, H) + 1e-5 * reach);
+    F.centre_d = static_cast<float>(d0 + 1e-5 * reach);
+    F.reach = static_cast<float>(reach);
+    F.dx = static_cast<float>(dx);
+    F.dy = static_cast<float>(dy);
+    F.sx = static_cast<float>(1.0 / dx);
+    F.sy = static_cast<float>(1.0 / dy);
+    F.ox = static_cast<float>(-(lo[0] - margin) / dx);
+    F.oy = static_cast<float>(-(lo[1] - margin) / dy);
+    // values lie within [-half size, diagonal of the grid]
+    F.base = static_cast<float>(-0.6 * std::hypot(W, H) - 2.0 * std::hypot(dx, dy));
+    F.quantum = static_cast<float>((1.6 * std::hypot(w0, h0) + 3.0 * std::hypot(dx, dy)) / 65000.0);
+    F.err_cell = static_cast<float>(0.51 * std::hypot(dx, dy) + F.quantum + 1e-5 * reach);
+    // the gradient's components are rounded to 1 / 127
+    F.err_linear = static_cast<float>((dx + dy) * 0.26 / 127.0 + F.quantum + 1e-5 * reach);
+    return F;
+}
+
+// The footprint's bound table on the device (the stream is idle: set_footprint
+// waits before it changes what earlier steps read).
+int upload_foot(mppi_ctx ctx, DevBuf& buf, int kind, const float* host, int count) {
+    const FootTable F = foot_head(kind, host, count);
+    HIP_TRY(ctx, buf.ensure(foot_table_bytes()));
+    HIP_TRY(ctx, hipMemcpy(buf.p, &F, sizeof F, hipMemcpyHostToDevice));
+    HIP_TRY(ctx, launch_foot_table(kind, buf.as<FootTable>(),
+                                   kind == 0 ? ctx->poly_tab_a.as<float4>() : ctx->rects.as<float4>(),
+                                   kind == 0 ? ctx->poly_tab_b.as<float4>() : nullptr, count, ctx->stream));
+    HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+    return MPPI_OK;
+}
+
+}  // namespace
+
 extern "C" {
 
 int mppi_create(mppi_ctx* out, int device, void* hip_stream) {
@@ -93,7 +156,9 @@ int mppi_destroy(mppi_ctx ctx) {
         (void)hipStreamSynchronize(ctx->stream);
         if (ctx->gbatch) mppi_batch_destroy(ctx->gbatch);
         DevBuf* bufs[] = {&ctx->poly_verts, &ctx->poly_tab_a, &ctx->poly_tab_b, &ctx->rects,
+                          &ctx->poly_foot, &ctx->rect_foot,
                           &ctx->px, &ctx->py, &ctx->pvx, &ctx->pvy, &ctx->pidx, &ctx->n_valid,
+                          &ctx->pxy, &ctx->leaf, &ctx->leaf_vel, &ctx->super, &ctx->points_ws,
                           &ctx->path, &ctx->cloud_keys, &ctx->cloud_first, &ctx->cloud_cell,
                           &ctx->cloud_r2, &ctx->cloud_misc,
                           &ctx->eps_ws, &ctx->poses_ws, &ctx->jbase, &ctx->jt,
@@ -160,9 +225,11 @@ int set_footprint(mppi_ctx ctx, int kind, const float* host, int count) {
     DeviceGuard g(ctx->device);
     if (kind == MPPI_FP_POLYGON) {
         const int BP = dmin_padded_count(0, count);
-        // padded vertex list for the fused kernel: repeats of vertex 0
-        std::vector<float> pv(2 * BP);
-        for (int b = 0; b < BP; ++b) {
+        // padded vertex list: repeats of vertex 0 up to the padded count, and
+        // for the distance pass's rows of 16 lanes to 16, 32 or 64
+        const int BQ = BP <= 16 ? 16 : BP <= 32 ? 32 : 64;
+        std::vector<float> pv(2 * BQ);
+        for (int b = 0; b < BQ; ++b) {
             const int s = b < count ? b : 0;
             pv[2 * b] = host[2 * s];
             pv[2 * b + 1] = host[2 * s + 1];
@@ -196,6 +263,7 @@ int set_footprint(mppi_ctx ctx, int kind, const float* host, int count) {
         HIP_TRY(ctx, hipMemcpy(ctx->poly_verts.p, pv.data(), pv.size() * sizeof(float), hipMemcpyHostToDevice));
         HIP_TRY(ctx, hipMemcpy(ctx->poly_tab_a.p, ta.data(), ta.size() * sizeof(float), hipMemcpyHostToDevice));
         HIP_TRY(ctx, hipMemcpy(ctx->poly_tab_b.p, tb.data(), tb.size() * sizeof(float), hipMemcpyHostToDevice));
+        if (int rc = upload_foot(ctx, ctx->poly_foot, kind, host, count)) return rc;
         ctx->B = count;
         ctx->BP = BP;
         ctx->has_poly = true;
@@ -209,6 +277,7 @@ int set_footprint(mppi_ctx ctx, int kind, const float* host, int count) {
         HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
         HIP_TRY(ctx, ctx->rects.ensure(rv.size() * sizeof(float)));
         HIP_TRY(ctx, hipMemcpy(ctx->rects.p, rv.data(), rv.size() * sizeof(float), hipMemcpyHostToDevice));
+        if (int rc = upload_foot(ctx, ctx->rect_foot, kind, host, count)) return rc;
         ctx->R = count;
         ctx->RP = RP;
         ctx->has_rect = true;
@@ -244,17 +313,21 @@ int set_points(mppi_ctx ctx, const float* dx, const float* dy, const float* dvx,
     HIP_TRY(ctx, ctx->px.ensure(cap * sizeof(float)));
     HIP_TRY(ctx, ctx->py.ensure(cap * sizeof(float)));
     HIP_TRY(ctx, ctx->pidx.ensure(cap * sizeof(int)));
+    const size_t leaves = (cap + LEAF_POINTS - 1) / LEAF_POINTS;
+    HIP_TRY(ctx, ctx->pxy.ensure(cap * (moving ? sizeof(float4) : sizeof(float2))));
+    HIP_TRY(ctx, ctx->leaf.ensure(leaves * sizeof(float4)));
+    HIP_TRY(ctx, ctx->super.ensure((leaves + SUPER_LEAVES - 1) / SUPER_LEAVES * sizeof(float4)));
+    HIP_TRY(ctx, ctx->points_ws.ensure(points_work_bytes(n)));
     if (moving) {
         HIP_TRY(ctx, ctx->pvx.ensure(cap * sizeof(float)));
         HIP_TRY(ctx, ctx->pvy.ensure(cap * sizeof(float)));
-        // a missing velocity component is zero
-        if (!dvx) HIP_TRY(ctx, hipMemsetAsync(ctx->pvx.p, 0, cap * sizeof(float), ctx->stream));
-        if (!dvy) HIP_TRY(ctx, hipMemsetAsync(ctx->pvy.p, 0, cap * sizeof(float), ctx->stream));
+        HIP_TRY(ctx, ctx->leaf_vel.ensure(leaves * sizeof(float4)));
     }
-    HIP_TRY(ctx, launch_compact_points(dx, dy, dvx, dvy, dvalid, n, ctx->px.as<float>(),
-                                       ctx->py.as<float>(), dvx ? ctx->pvx.as<float>() : nullptr,
-                                       dvy ? ctx->pvy.as<float>() : nullptr, ctx->pidx.as<int>(),
-                                       ctx->n_valid.as<int>(), ctx->stream));
+    // (a missing velocity component is zero)
+    const PointSet out{ctx->px.as<float>(), ctx->py.as<float>(), ctx->pvx.as<float>(), ctx->pvy.as<float>(),
+                       ctx->pidx.as<int>(), ctx->n_valid.as<int>(), ctx->pxy.as<float2>(),
+                       ctx->pxy.as<float4>(), ctx->leaf.as<float4>(), ctx->leaf_vel.as<float4>(), ctx->super.as<float4>()};
+    HIP_TRY(ctx, launch_points(dx, dy, dvx, dvy, dvalid, n, out, ctx->points_ws.p, ctx->stream));
     ctx->n_points = n;
     ctx->moving = moving;
     return MPPI_OK;
@@ -554,15 +627,32 @@ int mppi_autotune(mppi_ctx ctx, const mppi_params* prm, int reps, int* out_block
     hipEvent_t e0, e1;
     HIP_TRY(ctx, hipEventCreate(&e0));
     HIP_TRY(ctx, hipEventCreate(&e1));
+    // block 0: the default shape, which needs no entry
+    auto tune = [&](int poses, int block, int chunks) {
+        const auto k = std::make_tuple(kind, padded, ctx->moving ? 1 : 0, poses, ctx->n_points);
+        if (block)
+            ctx->tuned[k] = {block, chunks};
+        else
+            ctx->tuned.erase(k);
+    };
+    tune(npose, 0, 0);  // time without an earlier entry
+    tune(A.T, 0, 0);
     const int blocks[] = {64, 128, 256};
     const int chunk_counts[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 13, 16, 20, 24, 32, 40, 48, 64, 96, 128};
-    std::vector<std::pair<int, int>> cand;
-    // chunks of at least 32 points, 8 when there are few poses (the pass then
-    // needs the point chunks to fill the chip)
-    const int min_chunk = npose <= 16384 ? 8 : 32;
+    std::vector<std::pair<int, int>> cand{{0, 0}};  // the default shape
+    // chunk counts that the pass can take: ranges of the hierarchy, or (every
+    // point) chunks of at least 32 points, 8 when there are few poses (the pass
+    // then needs the point chunks to fill the chip)
+    const bool every = dmin_every(padded, ctx->n_points);
+    auto usable = [&](int nc, int min_chunk) {
+        if (every) return nc == 1 || ctx->n_points / nc >= min_chunk;
+        int supers, ranges;
+        dmin_ranges(ctx->n_points, nc, supers, ranges);
+        return ranges == nc;
+    };
     for (int b : blocks)
         for (int nc : chunk_counts)
-            if (nc == 1 || ctx->n_points / nc >= min_chunk) cand.emplace_back(b, nc);
+            if (usable(nc, npose <= 16384 ? 8 : 32)) cand.emplace_back(b, nc);
     std::vector<float> best(cand.size(), 1e30f);
     unsigned int* key = ctx->key.as<unsigned int>();
     int rc = MPPI_OK;
@@ -601,14 +691,14 @@ int mppi_autotune(mppi_ctx ctx, const mppi_params* prm, int reps, int* out_block
             best_c = cand[ci].second;
         }
     if (rc == MPPI_OK)
-        ctx->tuned[std::make_tuple(kind, padded, ctx->moving ? 1 : 0, npose, ctx->n_points)] = {best_b, best_c};
+        tune(npose, best_b, best_c);
     // the validation pass (T poses of the nominal, one 64-lane workgroup per
     // point chunk): its chunk count, timed on the first T sampled poses
     if (rc == MPPI_OK && prm->validate) {
-        const int nchunks[] = {8, 16, 32, 64, 128, 256, 512, 1024};
+        const int nchunks[] = {1, 2, 4, 8, 16, 32, 64, 128, 256, 512, 1024};
         std::vector<int> vc;
         for (int nc : nchunks)
-            if (nc == 8 || ctx->n_points / nc >= 8) vc.push_back(nc);
+            if (usable(nc, 8)) vc.push_back(nc);
         std::vector<float> vbest(vc.size(), 1e30f);
         const PoseTime ptn{1, A.T, A.state_offset, A.dt};
         HIP_TRY(ctx, ctx->key_nom.ensure(sizeof(unsigned int) * A.T));
@@ -636,14 +726,14 @@ int mppi_autotune(mppi_ctx ctx, const mppi_params* prm, int reps, int* out_block
             size_t bi = 0;
             for (size_t ci = 1; ci < vc.size(); ++ci)
                 if (vbest[ci] < vbest[bi]) bi = ci;
-            ctx->tuned[std::make_tuple(kind, padded, ctx->moving ? 1 : 0, A.T, ctx->n_points)] = {64, vc[bi]};
+            tune(A.T, every || vc[bi] > 1 ? 64 : 0, vc[bi]);
         }
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (rc) return rc;
-    if (out_block) *out_block = best_b;
-    if (out_nchunk) *out_nchunk = best_c;
+    if (out_block) *out_block = best_b ? best_b : 64;
+    if (out_nchunk) *out_nchunk = std::max(best_c, 1);
     return MPPI_OK;
 }
 

@@ -81,10 +81,11 @@ struct mppi_ctx_s {
     bool has_poly = false, has_rect = false;
     int B = 0, BP = 0, R = 0, RP = 0;
     DevBuf poly_verts, poly_tab_a, poly_tab_b, rects;
-    // obstacle points (compacted)
+    DevBuf poly_foot, rect_foot;  // bound tables (FootTable and its cells)
+    // obstacle points (compacted, in spatial order) and their hierarchy
     int n_points = 0;
     bool moving = false;
-    DevBuf px, py, pvx, pvy, pidx, n_valid;
+    DevBuf px, py, pvx, pvy, pidx, n_valid, pxy, leaf, leaf_vel, super, points_ws;
     // guidance polyline (fixed capacity MPPI_MAX_PATH waypoints, so the
     // address a captured graph holds stays valid)
     DevBuf path;
@@ -233,10 +234,15 @@ inline PointArgs point_args(mppi_ctx ctx) {
     pa.vy = ctx->moving ? ctx->pvy.as<float>() : nullptr;
     pa.idx = ctx->pidx.as<int>();
     pa.n_valid = ctx->n_valid.as<int>();
+    pa.xy = ctx->moving ? nullptr : ctx->pxy.as<float2>();
+    pa.xyv = ctx->moving ? ctx->pxy.as<float4>() : nullptr;
+    pa.leaf = ctx->n_points > emppi::POINTS_DIRECT_MAX ? ctx->leaf.as<float4>() : nullptr;
+    pa.leaf_vel = ctx->moving ? ctx->leaf_vel.as<float4>() : nullptr;
+    pa.super = ctx->super.as<float4>();
     return pa;
 }
 
-// Waves per SIMD the fused kernel runs at (its register budget), used to
+// Waves per SIMD the every-point kernels run at (its register budget), used to
 // estimate how many workgroups are resident at once.
 inline int dmin_waves_per_simd(int kind, int padded) {
     if (kind == 1) return 8;
@@ -245,7 +251,7 @@ inline int dmin_waves_per_simd(int kind, int padded) {
     return padded <= 8 ? 6 : padded <= 16 ? 4 : 3;
 }
 
-// Default tile shape: chunks of at least 32 points, and a workgroup count
+// Default tile shape of the every-point pass: chunks of at least 32 points, and a workgroup count
 // close to a whole number of "rounds" of resident workgroups so that the
 // last round is not a nearly empty tail (all workgroups do equal work).
 inline void choose_tiles(int kind, int padded, int npose, int n_points, int& block, int& nchunk, int& chunk) {
@@ -273,13 +279,39 @@ inline void choose_tiles(int kind, int padded, int npose, int n_points, int& blo
     nchunk = std::max(1, (n_points + chunk - 1) / chunk);
 }
 
+// Shape of the bounded search.  8 waves share one copy of the footprint's
+// table; the registers allow 24 waves per compute unit (16 for polygons above
+// 32 vertices).  The poses are dealt so that one round of resident
+// workgroups takes them all: with a part of a second round, the chip waits
+// for few workgroups as long as for many.  block = poses per workgroup (0:
+// that rule).
+constexpr int DMIN_WAVES = 8;
+constexpr int DMIN_MAX_POSES = 16;  // per wave and tile
+inline void dmin_shape(int kind, int padded, int npose, int block, int& poses_per_wave, int& tiles) {
+    const int waves = 256 * (kind == 0 && padded > 32 ? 16 : 24);
+    const int n = block ? block / DMIN_WAVES : std::max(1, (npose + waves - 1) / waves);
+    tiles = (n + DMIN_MAX_POSES - 1) / DMIN_MAX_POSES;
+    poses_per_wave = (n + tiles - 1) / tiles;
+}
+
+// Super nodes per point range for a requested chunk count.  A range's search
+// does not see the others' minima, so a range holds at least 64 super nodes
+// (32768 points) and smaller sets are not split.
+inline void dmin_ranges(int n_points, int want, int& supers, int& nchunk) {
+    const int per = emppi::LEAF_POINTS * emppi::SUPER_LEAVES;
+    const int total = std::max(1, (n_points + per - 1) / per);
+    supers = std::max(std::min(total, 64), (total + want - 1) / std::max(1, want));
+    nchunk = std::max(1, (total + supers - 1) / supers);
+}
+
 // Launch shape of the fused transform + signed distance + min stage.
 inline DminLaunch dmin_launch(mppi_ctx ctx, const float4* poses, int npose, PoseTime pt, int kind,
                               unsigned int* key, unsigned long long* key64, int force_block = 0,
                               int force_nchunk = 0) {
     const int padded = kind == 0 ? ctx->BP : ctx->RP;
-    int block, nchunk, chunk;
-    choose_tiles(kind, padded, npose, ctx->n_points, block, nchunk, chunk);
+    const bool every = emppi::dmin_every(padded, ctx->n_points);
+    int block = 0, nchunk = 1, chunk = 0;  // block 0: the default shape
+    if (every) choose_tiles(kind, padded, npose, ctx->n_points, block, nchunk, chunk);
     const auto it = ctx->tuned.find(std::make_tuple(kind, padded, ctx->moving ? 1 : 0, npose, ctx->n_points));
     if (it != ctx->tuned.end()) {
         block = it->second.first;
@@ -291,19 +323,25 @@ inline DminLaunch dmin_launch(mppi_ctx ctx, const float4* poses, int npose, Pose
     }
     if (force_block) block = force_block;
     if (force_nchunk) nchunk = force_nchunk;
-    chunk = std::max(1, (ctx->n_points + nchunk - 1) / nchunk);
-    nchunk = std::max(1, (ctx->n_points + chunk - 1) / chunk);
     DminLaunch L{};
     L.poses = poses;
     L.npose = npose;
     L.pt = pt;
     L.pts = point_args(ctx);
-    L.chunk = chunk;
-    L.nchunk = nchunk;
-    L.block = block;
+    L.every = every;
+    if (every) {
+        L.chunk = std::max(1, (ctx->n_points + nchunk - 1) / nchunk);
+        L.nchunk = std::max(1, (ctx->n_points + L.chunk - 1) / L.chunk);
+        L.block = block;
+    } else {
+        L.waves = DMIN_WAVES;
+        dmin_shape(kind, padded, npose, block, L.poses_per_wave, L.tiles);
+        dmin_ranges(ctx->n_points, nchunk, L.supers, L.nchunk);
+    }
     L.kind = kind;
     L.verts = ctx->poly_verts.as<float2>();
     L.rects = ctx->rects.as<float4>();
+    L.foot = (kind == 0 ? ctx->poly_foot : ctx->rect_foot).as<emppi::FootTable>();
     L.padded = padded;
     L.argmin = key64 != nullptr;
     L.key = key;

@@ -89,4 +89,28 @@ inline int polygon_defect(const std::vector<double>& v, int B, char* msg, size_t
     return 0;
 }
 
+// Signed distance of (x, y) to the polygon of B vertices v = (x0, y0, ...),
+// or to the cover of B boxes v = (centre, half extents): negative inside.
+inline double polygon_distance(const double* v, int B, double x, double y) {
+    double best = INFINITY;
+    bool inside = false;
+    for (int b = 0; b < B; ++b) {
+        const double* p = v + 2 * b;
+        const double* q = v + 2 * ((b + 1) % B);
+        const double ex = q[0] - p[0], ey = q[1] - p[1], wx = x - p[0], wy = y - p[1];
+        const double t = std::min(1.0, std::max(0.0, (wx * ex + wy * ey) / (ex * ex + ey * ey)));
+        best = std::min(best, std::hypot(wx - t * ex, wy - t * ey));
+        if ((p[1] > y) != (q[1] > y) && x < p[0] + (y - p[1]) * ex / ey) inside = !inside;
+    }
+    return inside ? -best : best;
+}
+inline double cover_distance(const double* v, int R, double x, double y) {
+    double best = INFINITY;
+    for (int j = 0; j < R; ++j) {
+        const double ax = std::fabs(x - v[4 * j]) - v[4 * j + 2], ay = std::fabs(y - v[4 * j + 1]) - v[4 * j + 3];
+        best = std::min(best, std::hypot(std::max(ax, 0.0), std::max(ay, 0.0)) + std::min(std::max(ax, ay), 0.0));
+    }
+    return best;
+}
+
 }  // namespace emppi_host

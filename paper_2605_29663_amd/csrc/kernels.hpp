@@ -7,6 +7,17 @@ namespace emppi {
 
 constexpr int WAVE = 64;
 constexpr int DMIN_TILE = 1024;      // points staged in LDS per tile
+// Bounding hierarchy over the spatially ordered points (kernels_points.hip).
+// 8 points per leaf: with 16, the leaves that survive a pose's test hold
+// about twice as many points, with 4 the leaf tests cost as much as the
+// point tests they save.  64 leaves per super node: one per lane.
+constexpr int LEAF_POINTS = 8;
+constexpr int SUPER_LEAVES = 64;
+// Sets without a hierarchy: bounding all of 512 points takes a pose 8 lane
+// batches, about as many as the hierarchy's tests and the points they leave,
+// and the order costs set_points 4 us.
+constexpr int POINTS_DIRECT_MAX = 512;
+constexpr int POINTS_SMALL_MAX = 1 << 15;  // sets prepared by one workgroup
 constexpr int MPPI_MAX_T_DEV = 128;  // horizon capacity (MPPI_MAX_T of the C ABI)
 // Per-step result record: u*_0, u*_1, u*_2, valid, J_nom (noise-free cost of
 // the validated nominal), then padding.
@@ -25,8 +36,13 @@ struct StepArgs {
     float w_path;
 };
 
-// Valid obstacle points, compacted in index order (the count lives on the
-// device so that a mask change needs no host round trip).
+// Valid obstacle points, compacted in spatial order (the count lives on the
+// device so that a mask change needs no host round trip), with their
+// bounding hierarchy: leaf l covers points [8 l, 8 l + 8): (x, y) of one of
+// them, the largest distance from it to the others, unused; leaf_vel: that
+// point's velocity and the largest velocity difference to it; super node s
+// covers leaves [64 s, 64 s + 64): centre and radius of a circle around
+// them, and their largest speed.
 struct PointArgs {
     const float* x;
     const float* y;
@@ -34,7 +50,66 @@ struct PointArgs {
     const float* vy;
     const int* idx;   // caller's index of each compacted point
     const int* n_valid;
+    const float2* xy;        // static sets: (x, y) of each point
+    const float4* xyv;       // moving sets: (x, y, vx, vy)
+    const float4* leaf;      // nullptr: no hierarchy (at most POINTS_DIRECT_MAX points)
+    const float4* leaf_vel;  // moving sets only
+    const float4* super;
 };
+
+// The same buffers as set_points fills them.
+struct PointSet {
+    float *x, *y, *vx, *vy;
+    int *idx, *n_valid;
+    float2* xy;   // one of xy and xyv
+    float4 *xyv, *leaf, *leaf_vel, *super;
+};
+
+// Workspace of the many-workgroup preparation.
+struct PointWork {
+    unsigned* positions;  // output position per point, ~0 if masked (above 8192 points)
+    uint2* cell_rank;     // this and the rest above POINTS_SMALL_MAX
+    unsigned* cells;
+    int* block_sums;
+    float* grid;  // lo x, lo y, cells per metre x, y
+};
+size_t points_work_bytes(int n);
+hipError_t launch_points(const float* x, const float* y, const float* vx, const float* vy,
+                         const unsigned char* valid, int n, const PointSet& out, void* work, hipStream_t s);
+
+// Bounds of a footprint's signed distance on a grid of cells in the body
+// frame, at the head of a device buffer that the cells follow.  A cell is one
+// word, (v, gx, gy) in bits 0-15, 16-23 and 24-31 (gx, gy signed): the
+// distance at its centre lies in [base + quantum v, base + quantum (v + 1)].
+// Where one straight feature is nearest to the whole cell the distance is
+// linear in it, with the gradient (gx, gy) / 127, and est = base + quantum v
+// + gradient . offset from the centre is exact to err_linear; elsewhere gx =
+// gy = 0 and est is exact to err_cell, half the cell's diagonal (the distance
+// changes by at most the way travelled).  The grid covers the footprint's
+// bounding box and a margin around it, in which every border cell's lower
+// bound is positive; a point outside projects onto the grid's rectangle,
+// which is convex, so with the distance a to the projection and the
+// projection's bounds [lb, ub] its distance lies in
+// [sqrt(lb^2 + a^2), ub + a].
+struct FootTable {
+    float cx, cy;      // centre of the bounding box
+    float radius;      // of a circle around (cx, cy) that holds the footprint
+    float centre_d;    // signed distance at (cx, cy), rounded up
+    float reach;       // largest distance of the footprint from the body origin
+    float sx, sy;      // cells per metre
+    float ox, oy;      // cell coordinate of the body origin
+    float dx, dy;      // metres per cell
+    float base, quantum, err_cell, err_linear;
+    int nx, ny;
+    int pad_[15];
+};
+static_assert(sizeof(FootTable) == 128, "the cells start 128 bytes into the buffer");
+constexpr int FOOT_CELLS = 4096;  // most cells of a table (16 KB of LDS)
+inline size_t foot_table_bytes() { return sizeof(FootTable) + sizeof(uint32_t) * FOOT_CELLS; }
+// Fill the cells of the table at `table` (its head is already there) from
+// the point-wise tables of the footprint (launch_sdf_points).
+hipError_t launch_foot_table(int kind, FootTable* table, const float4* tab_a, const float4* tab_b,
+                             int count, hipStream_t s);
 
 // Time of pose g for moving points: h = (g / div) % mod, t = (h + off) dt.
 struct PoseTime {
@@ -63,18 +138,35 @@ __device__ __forceinline__ float dkey_distance(unsigned int k) {
     return sq < 0.0f ? -__builtin_sqrtf(-sq) : __builtin_sqrtf(sq);
 }
 
+// The distance pass evaluates every point (kernels_sdf_every.hip) of sets
+// that keep the caller's order while that takes fewer instructions than the
+// bounded search (cull_device.hpp): (10.75 padded + 6) / 64 per point and pose
+// against about 600 per pose at 512 points (measured at 512 points, 5120
+// poses, 8 vertices: 9.6 against 14.5 us; the sets' sizes where the two meet
+// follow 1 / vertices).
+inline bool dmin_every(int padded, int n_points) {
+    return n_points <= POINTS_DIRECT_MAX && n_points * (10.75 * padded + 6.0) <= 50000.0;
+}
+
 // One launch of the fused transform + signed distance + min-over-points
-// stage: npose poses, points split into nchunk chunks of `chunk` points;
-// each (pose, chunk) minimum is merged into key[g] (or key64[g]).
+// stage over npose poses.  Search: a workgroup of `waves` waves takes `tiles`
+// tiles of poses_per_wave poses per wave; the point hierarchy is split into
+// nchunk ranges of `supers` super nodes.  Every point: one lane (group) per
+// pose, `block` threads, nchunk chunks of `chunk` points.  Each (pose, chunk
+// or range) minimum is merged into key[g] (or key64[g]).
 struct DminLaunch {
     const float4* poses;
     int npose;
     PoseTime pt;
     PointArgs pts;
-    int chunk, nchunk, block;
+    bool every;
+    int waves, poses_per_wave, tiles, supers;
+    int block, chunk;
+    int nchunk;
     int kind;          // 0 polygon, 1 rectangle cover
-    const float2* verts;  // polygon, padded to `padded` vertices (repeats of v0)
+    const float2* verts;  // polygon, padded to `padded` vertices and to 16, 32 or 64 (repeats of v0)
     const float4* rects;  // rectangle cover, padded to `padded` boxes (repeats of box 0)
+    const FootTable* foot;  // bound table of that footprint
     int padded;
     bool argmin;
     unsigned int* key;         // [npose], initialised to DKEY_INIT
@@ -82,6 +174,7 @@ struct DminLaunch {
 };
 
 hipError_t launch_dmin(const DminLaunch& L, hipStream_t s);
+hipError_t launch_dmin_every(const DminLaunch& L, hipStream_t s);
 int dmin_padded_count(int kind, int count);  // bucket a footprint size is padded to
 
 hipError_t launch_key_init(unsigned int* key, unsigned long long* key64, int n, hipStream_t s);
@@ -91,10 +184,6 @@ hipError_t launch_dmin_finalize(const unsigned int* key, const unsigned long lon
 hipError_t launch_sdf_points(int kind, const float* px, const float* py, int n,
                              const float4* tab_a, const float4* tab_b, int count, float* out,
                              hipStream_t s);
-
-hipError_t launch_compact_points(const float* x, const float* y, const float* vx, const float* vy,
-                                 const unsigned char* valid, int n, float* ox, float* oy,
-                                 float* ovx, float* ovy, int* oidx, int* n_valid, hipStream_t s);
 
 struct RolloutOut {
     const float* useq = nullptr;  // [K][T][nu] given control sequences (no noise), or nullptr

@@ -77,7 +77,10 @@ __global__ __launch_bounds__(1024) void k_features(const float* __restrict__ px,
         }
         const int bin = q * 16 + min(15, static_cast<int>(t * 16.0f));
         const float r = seq_sqrt(x * x + y * y);
-        atomicMin(&hist[bin], __float_as_uint(fminf(r, F.r_max)));
+        // neighbouring points share bins (the set is in spatial order), so a
+        // read first spares most of the atomics: a bin's minimum only falls
+        const unsigned int rb = __float_as_uint(fminf(r, F.r_max));
+        if (rb < *static_cast<volatile unsigned int*>(&hist[bin])) atomicMin(&hist[bin], rb);
     }
     __syncthreads();
     for (int b = threadIdx.x; b < FEAT_BINS; b += blockDim.x) out[b] = __uint_as_float(hist[b]) / F.r_max;

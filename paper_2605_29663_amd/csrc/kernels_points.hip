@@ -1,0 +1,629 @@
+// Obstacle-set preparation of set_points: the validity mask, a spatial order
+// of the valid points, and the two-level bounding hierarchy that the
+// signed-distance pass searches (LEAF_POINTS points per leaf, SUPER_LEAVES
+// leaves per super node).
+//
+// The points are counted into the cells of a Z-order grid over the point
+// set's bulk (quantiles of a 64-point sample, so that a few far outliers do
+// not coarsen the grid; points outside go to the border cells), the cell
+// counts are summed, and every point moves to its cell's range.  Points of
+// one cell keep no particular order: the distance pass takes exact minima,
+// which do not depend on it, and every point carries the caller's index.
+//
+// Up to POINTS_SMALL_MAX points one workgroup sorts in LDS: the point arrays
+// are a few hundred KB, so the pass is a chain of memory and barrier
+// latencies, and one launch is shorter than the five that a grid needs.
+// Larger sets take the multi-workgroup path.
+#include "kernels.hpp"
+#include "wave_ops.hpp"
+
+namespace emppi {
+
+namespace {
+
+constexpr int SMALL_THREADS = 1024;
+constexpr int WINDOW = 8192;  // sorted points in LDS at a time (half as many moving ones)
+constexpr int LARGE_CELL_BITS = 18;
+
+// Z-order of two coordinates below 2^16 packed as y << 16 | x: the bits of x
+// at the even positions, those of y at the odd ones.  Both halves are spread
+// at once while they stay below 2^8.
+__device__ __forceinline__ unsigned spread16(unsigned v) {
+    v = (v | (v << 4)) & 0x0F0F0F0Fu;
+    v = (v | (v << 2)) & 0x33333333u;
+    return (v | (v << 1)) & 0x55555555u;
+}
+__device__ __forceinline__ unsigned z_order(unsigned x, unsigned y) {
+    const unsigned lo = spread16((x & 0xFFu) | ((y & 0xFFu) << 16));
+    const unsigned z = (lo & 0xFFFFu) | (lo >> 15);
+    const unsigned hx = x >> 8, hy = y >> 8;
+    if (__builtin_expect((hx | hy) == 0, 1)) return z;
+    const unsigned hi = spread16(hx | (hy << 16));
+    return z | (((hi & 0xFFFFu) | (hi >> 15)) << 16);
+}
+
+// The grid over the bulk of the points: cell coordinate = (p - lo) * scale.
+struct Grid {
+    float lox, loy, sx, sy;
+};
+
+// Cell of a point: Z-order of (cell_bits + 1) / 2 bits in x and cell_bits / 2
+// in y; moving points of a mixed set (split) take the upper half of the
+// cells, so that leaves hold points of one kind.
+__device__ __forceinline__ unsigned cell_of(const Grid& G, int cell_bits, bool split, bool moves,
+                                            float x, float y) {
+    const int bits = split ? cell_bits - 1 : cell_bits;
+    const int bx = (bits + 1) / 2, by = bits / 2;
+    const float fx = __builtin_amdgcn_fmed3f((x - G.lox) * G.sx, 0.0f, static_cast<float>((1 << bx) - 1));
+    const float fy = __builtin_amdgcn_fmed3f((y - G.loy) * G.sy, 0.0f, static_cast<float>((1 << by) - 1));
+    const unsigned c = z_order(static_cast<unsigned>(fx), static_cast<unsigned>(fy));
+    return c | (split && moves ? 1u << bits : 0u);
+}
+
+struct PointIn {
+    const float *x, *y, *vx, *vy;  // vx, vy may be nullptr
+    const unsigned char* valid;    // may be nullptr
+    int n;
+};
+
+__device__ __forceinline__ bool point_ok(const PointIn& in, int i) {
+    bool ok = isfinite(in.x[i]) && isfinite(in.y[i]);
+    if (in.vx) ok = ok && isfinite(in.vx[i]);
+    if (in.vy) ok = ok && isfinite(in.vy[i]);
+    if (in.valid) ok = ok && in.valid[i] != 0;
+    return ok;
+}
+
+__device__ __forceinline__ bool point_moves(const PointIn& in, int i) {
+    return (in.vx && in.vx[i] != 0.0f) || (in.vy && in.vy[i] != 0.0f);
+}
+
+// One coordinate's grid range from a 64-point sample (one wave, all lanes):
+// the 1/16 and 15/16 quantiles of the valid samples, widened by 1/4 of
+// their distance on both sides; returns (lo, cells per metre).
+__device__ float2 sample_range(const PointIn& in, const float* a, int cells) {
+    const int lane = threadIdx.x & (WAVE - 1);
+    const int i = static_cast<int>(static_cast<long long>(lane) * in.n / WAVE);
+    const bool ok = in.n > 0 && point_ok(in, i);
+    const float v = ok ? a[i] : INFINITY;
+    const int count = __popcll(__ballot(ok));
+    int rank = 0;
+#pragma unroll
+    for (int j = 0; j < WAVE; ++j) {
+        const float w = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), j));
+        rank += (w < v || (w == v && j < lane)) ? 1 : 0;
+    }
+    if (count == 0) return make_float2(0.0f, 0.0f);
+    const uint64_t at_lo = __ballot(rank == count / 16), at_hi = __ballot(rank == count - 1 - count / 16);
+    const float qlo = __shfl(v, __ffsll(static_cast<long long>(at_lo)) - 1);
+    const float qhi = __shfl(v, __ffsll(static_cast<long long>(at_hi)) - 1);
+    const float wide = 0.25f * (qhi - qlo);
+    const float lo = qlo - wide, span = (qhi + wide) - lo;
+    const bool usable = span > 0.0f && span < 1e30f;
+    return make_float2(lo, usable ? static_cast<float>(cells) / span : 0.0f);
+}
+
+// Leaf over the points at(k) = (x, y, vx, vy), k < LEAF_POINTS (any repeated):
+// the point nearest to the centre of their bounding box represents the leaf;
+// radius = the largest distance to it, rv the largest velocity difference.
+template <bool MOVING, typename At>
+__device__ __forceinline__ void make_leaf(At&& at, float4& leaf, float4& vel) {
+    float4 p[LEAF_POINTS];
+    float x0 = INFINITY, x1 = -INFINITY, y0 = INFINITY, y1 = -INFINITY;
+#pragma unroll
+    for (int k = 0; k < LEAF_POINTS; ++k) {
+        p[k] = at(k);
+        x0 = fminf(x0, p[k].x);
+        x1 = fmaxf(x1, p[k].x);
+        y0 = fminf(y0, p[k].y);
+        y1 = fmaxf(y1, p[k].y);
+    }
+    const float cx = 0.5f * x0 + 0.5f * x1, cy = 0.5f * y0 + 0.5f * y1;
+    float best = INFINITY;
+    float4 rep = p[0];
+#pragma unroll
+    for (int k = 0; k < LEAF_POINTS; ++k) {
+        const float dx = p[k].x - cx, dy = p[k].y - cy, d = dx * dx + dy * dy;
+        if (d < best) {
+            best = d;
+            rep = p[k];
+        }
+    }
+    float r2 = 0.0f, v2 = 0.0f;
+#pragma unroll
+    for (int k = 0; k < LEAF_POINTS; ++k) {
+        const float dx = p[k].x - rep.x, dy = p[k].y - rep.y;
+        r2 = fmaxf(r2, dx * dx + dy * dy);
+        if (MOVING) {
+            const float ux = p[k].z - rep.z, uy = p[k].w - rep.w;
+            v2 = fmaxf(v2, ux * ux + uy * uy);
+        }
+    }
+    // rounded up: the radius bounds the true distances
+    leaf = make_float4(rep.x, rep.y, __builtin_sqrtf(r2) * 1.00001f, 0.0f);
+    if (MOVING) vel = make_float4(rep.z, rep.w, __builtin_sqrtf(v2) * 1.00001f, 0.0f);
+}
+
+// Super node over a wave's 64 leaves (lane = leaf, on: the leaf exists):
+// centre and radius of a circle around them, and the largest speed.
+template <bool MOVING>
+__device__ __forceinline__ float4 make_super(bool on, float4 leaf, float4 vel) {
+    const float x0 = wave_min(on ? leaf.x : INFINITY), x1 = -wave_min(on ? -leaf.x : INFINITY);
+    const float y0 = wave_min(on ? leaf.y : INFINITY), y1 = -wave_min(on ? -leaf.y : INFINITY);
+    const float cx = 0.5f * x0 + 0.5f * x1, cy = 0.5f * y0 + 0.5f * y1;
+    const float dx = leaf.x - cx, dy = leaf.y - cy;
+    const float r = __builtin_sqrtf(dx * dx + dy * dy) * 1.00001f + leaf.z;
+    float v = 0.0f;
+    if (MOVING) v = __builtin_sqrtf(vel.x * vel.x + vel.y * vel.y) * 1.00001f + vel.z;
+    return make_float4(cx, cy, -wave_min(on ? -r : INFINITY), MOVING ? -wave_min(on ? -v : INFINITY) : 0.0f);
+}
+
+// ------------------------------------------------------------ few points
+// Up to POINTS_DIRECT_MAX points keep the caller's order and get no
+// hierarchy (the distance pass bounds every point of so small a set):
+// order-preserving compaction, one point per thread.
+__global__ __launch_bounds__(POINTS_DIRECT_MAX) void k_points_direct(PointIn in, PointSet out, bool moving) {
+    __shared__ int wsum[POINTS_DIRECT_MAX / WAVE];
+    const int t = threadIdx.x, lane = t & (WAVE - 1), wid = t / WAVE;
+    const int i = min(t, max(in.n - 1, 0));
+    float x = 0.f, y = 0.f, vx = 0.f, vy = 0.f;
+    bool ok = t < in.n;
+    if (in.n > 0) {
+        x = in.x[i];
+        y = in.y[i];
+        vx = in.vx ? in.vx[i] : 0.0f;
+        vy = in.vy ? in.vy[i] : 0.0f;
+        const unsigned char va = in.valid ? in.valid[i] : 1;
+        ok = ok && isfinite(x) && isfinite(y) && isfinite(vx) && isfinite(vy) && va != 0;
+    }
+    const unsigned long long m = __ballot(ok);
+    if (lane == 0) wsum[wid] = __popcll(m);
+    __syncthreads();
+    int base = 0, total = 0;
+    for (int w = 0; w < POINTS_DIRECT_MAX / WAVE; ++w) {
+        base += w < wid ? wsum[w] : 0;
+        total += wsum[w];
+    }
+    if (ok) {
+        const int o = base + __popcll(m & ((1ull << lane) - 1ull));
+        out.x[o] = x;
+        out.y[o] = y;
+        if (moving) {
+            out.vx[o] = vx;
+            out.vy[o] = vy;
+            out.xyv[o] = make_float4(x, y, vx, vy);
+        } else {
+            out.xy[o] = make_float2(x, y);
+        }
+        out.idx[o] = i;
+    }
+    if (t == 0) *out.n_valid = total;
+}
+
+// ------------------------------------------------------------ one workgroup
+// PT points per thread (n <= 1024 PT).  LDS: 16-bit cell counts (two per
+// word) and the exclusive sums of their groups of 8; the counts' space is
+// reused for the sorted points.  With PT <= 8 the points leave through LDS
+// in sorted order, coalesced, and the leaves are formed there; above, the
+// kernel stores every point's position (~0: masked) and k_points_place and
+// k_points_nodes finish with many workgroups (one workgroup's scattered
+// traffic would take longer than two more launches).
+template <int PT, bool MOVING>
+__global__ __launch_bounds__(SMALL_THREADS) void k_points_small(PointIn in, PointSet out, int cell_bits,
+                                                                unsigned* __restrict__ positions) {
+    constexpr bool PLACE = PT <= 8;
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ Grid grid;
+    __shared__ int wsum[SMALL_THREADS / WAVE];
+    const int t = threadIdx.x, lane = t & (WAVE - 1), wid = t / WAVE;
+    const int ncell = 1 << cell_bits;
+    unsigned* hist = reinterpret_cast<unsigned*>(smem);
+    uint4* h4 = reinterpret_cast<uint4*>(hist);
+    unsigned short* group = reinterpret_cast<unsigned short*>(hist + ncell / 2);
+    // the sample's range (waves 0 and 1) while the others clear the counts
+    const int grid_bits = MOVING ? cell_bits - 1 : cell_bits;
+    if (wid == 0) {
+        const float2 r = sample_range(in, in.x, 1 << ((grid_bits + 1) / 2));
+        if (lane == 0) {
+            grid.lox = r.x;
+            grid.sx = r.y;
+        }
+    } else if (wid == 1) {
+        const float2 r = sample_range(in, in.y, 1 << (grid_bits / 2));
+        if (lane == 0) {
+            grid.loy = r.x;
+            grid.sy = r.y;
+        }
+    }
+    for (int c = t; c < ncell / 8; c += SMALL_THREADS) h4[c] = make_uint4(0, 0, 0, 0);
+    // every load of a batch is issued before the first result is used
+    constexpr int HV = MOVING && PLACE ? PT : 1;  // velocities held
+    constexpr int BATCH = PT < 8 ? PT : 8;
+    float px[PT], py[PT], pvx[HV], pvy[HV];
+    unsigned cr[PT];  // cell << 16 | rank within the cell; later the output position
+    unsigned okm = 0, mvm = 0;
+#pragma unroll
+    for (int k0 = 0; k0 < PT; k0 += BATCH) {
+        float vx[BATCH], vy[BATCH];
+        unsigned char va[BATCH];
+#pragma unroll
+        for (int b = 0; b < BATCH; ++b) {
+            const int i = min(t + (k0 + b) * SMALL_THREADS, max(in.n - 1, 0));
+            if (in.n > 0) {
+                px[k0 + b] = in.x[i];
+                py[k0 + b] = in.y[i];
+                vx[b] = MOVING && in.vx ? in.vx[i] : 0.0f;
+                vy[b] = MOVING && in.vy ? in.vy[i] : 0.0f;
+                va[b] = in.valid ? in.valid[i] : 1;
+            }
+        }
+#pragma unroll
+        for (int b = 0; b < BATCH; ++b) {
+            const int k = k0 + b;
+            const bool ok = t + k * SMALL_THREADS < in.n && isfinite(px[k]) && isfinite(py[k]) && va[b] != 0 &&
+                            (!MOVING || (isfinite(vx[b]) && isfinite(vy[b])));
+            okm |= ok ? 1u << k : 0u;
+            if (MOVING) mvm |= vx[b] != 0.0f || vy[b] != 0.0f ? 1u << k : 0u;
+            if (HV == PT) {
+                pvx[k % HV] = vx[b];
+                pvy[k % HV] = vy[b];
+            }
+        }
+    }
+    __syncthreads();
+    const Grid G = grid;
+#pragma unroll
+    for (int k = 0; k < PT; ++k) {
+        cr[k] = 0;
+        if (okm >> k & 1) {
+            const unsigned c = cell_of(G, cell_bits, MOVING, mvm >> k & 1, px[k], py[k]);
+            const unsigned sh = (c & 1) * 16;
+            cr[k] = (c << 16) | ((atomicAdd(&hist[c >> 1], 1u << sh) >> sh) & 0xFFFFu);
+        }
+    }
+    __syncthreads();
+    // exclusive sums of the groups of 8 cells in cell order: wave w owns the
+    // groups [w, w + 1) ncell / 128, one per lane and step (at most 8 steps)
+    const int own = ncell / 8 / (SMALL_THREADS / WAVE);  // groups per wave
+    const int per = min(own, WAVE);                      // groups per step
+    int sum[8];
+    int total = 0;
+#pragma unroll
+    for (int st = 0; st < 8; ++st) {
+        sum[st] = 0;
+        if (st * WAVE < own) {
+            const uint4 v = lane < per ? h4[wid * own + st * WAVE + lane] : make_uint4(0, 0, 0, 0);
+            // at most 2^15 points: the 16-bit halves cannot carry
+            const unsigned p = v.x + v.y + v.z + v.w;
+            sum[st] = static_cast<int>((p & 0xFFFFu) + (p >> 16));
+            total += sum[st];
+        }
+    }
+    total = wave_sum(total);
+    if (lane == 0) wsum[wid] = total;
+    __syncthreads();
+    int base = 0, nv = 0;
+    for (int w = 0; w < SMALL_THREADS / WAVE; ++w) {
+        base += w < wid ? wsum[w] : 0;
+        nv += wsum[w];
+    }
+#pragma unroll
+    for (int st = 0; st < 8; ++st)
+        if (st * WAVE < own) {
+            const int incl = wave_scan(sum[st]);
+            if (lane < per) group[wid * own + st * WAVE + lane] = static_cast<unsigned short>(base + incl - sum[st]);
+            base += __builtin_amdgcn_readlane(incl, WAVE - 1);
+        }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < PT; ++k)
+        if (okm >> k & 1) {
+            // the group's sum, the counts of its cells before this one, the rank
+            const unsigned c = cr[k] >> 16, in8 = c & 7;
+            const uint4 v = h4[c >> 3];
+            const unsigned odd = (in8 & 1) ? 0xFFFFu : 0u;  // the word of the cell: its lower half when odd
+            const unsigned m0 = in8 >= 2 ? ~0u : odd, m1 = in8 >= 4 ? ~0u : in8 >= 2 ? odd : 0u;
+            const unsigned m2 = in8 >= 6 ? ~0u : in8 >= 4 ? odd : 0u, m3 = in8 >= 6 ? odd : 0u;
+            const unsigned p = (v.x & m0) + (v.y & m1) + (v.z & m2) + (v.w & m3);
+            cr[k] = (cr[k] & 0xFFFFu) + group[c >> 3] + (p & 0xFFFFu) + (p >> 16);
+        }
+    if (t == 0) *out.n_valid = nv;
+    if (!PLACE) {
+#pragma unroll
+        for (int k = 0; k < PT; ++k) {
+            const int i = t + k * SMALL_THREADS;
+            if (i < in.n) positions[i] = okm >> k & 1 ? cr[k] : ~0u;
+        }
+        return;
+    }
+    __syncthreads();  // the counts are no longer read
+    // sorted points in LDS, WINDOW at a time, each array 16-byte aligned
+    const int nleaf = (nv + LEAF_POINTS - 1) / LEAF_POINTS;
+    constexpr int W = MOVING ? WINDOW / 2 : WINDOW;
+    const int W8 = (min(W, in.n) + 7) & ~7;
+    float* stx = reinterpret_cast<float*>(smem);
+    float *sty = stx + W8, *stvx = stx + 2 * W8, *stvy = stx + 3 * W8;
+    unsigned short* sti = reinterpret_cast<unsigned short*>(stx + (MOVING ? 4 : 2) * W8);
+    for (int w0 = 0; w0 < nv; w0 += W) {
+        const int wn = min(W, nv - w0);
+#pragma unroll
+        for (int k = 0; k < PT; ++k) {
+            const int pos = static_cast<int>(cr[k]) - w0;
+            if ((okm >> k & 1) && pos >= 0 && pos < wn) {
+                stx[pos] = px[k];
+                sty[pos] = py[k];
+                if (MOVING) {
+                    stvx[pos] = pvx[k % HV];
+                    stvy[pos] = pvy[k % HV];
+                }
+                sti[pos] = static_cast<unsigned short>(t + k * SMALL_THREADS);
+            }
+        }
+        __syncthreads();
+        for (int j = t; j < wn; j += SMALL_THREADS) {
+            out.x[w0 + j] = stx[j];
+            out.y[w0 + j] = sty[j];
+            if (MOVING) {
+                out.vx[w0 + j] = stvx[j];
+                out.vy[w0 + j] = stvy[j];
+                out.xyv[w0 + j] = make_float4(stx[j], sty[j], stvx[j], stvy[j]);
+            } else {
+                out.xy[w0 + j] = make_float2(stx[j], sty[j]);
+            }
+            out.idx[w0 + j] = sti[j];
+        }
+        for (int l = t; l * LEAF_POINTS < wn; l += SMALL_THREADS) {
+            // 8 points per leaf as two 16-byte reads per array
+            float x[LEAF_POINTS], y[LEAF_POINTS], vx[LEAF_POINTS], vy[LEAF_POINTS];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                auto get = [&](const float* a, float* o) {
+                    const float4 v = reinterpret_cast<const float4*>(a)[2 * l + h];
+                    o[4 * h] = v.x;
+                    o[4 * h + 1] = v.y;
+                    o[4 * h + 2] = v.z;
+                    o[4 * h + 3] = v.w;
+                };
+                get(stx, x);
+                get(sty, y);
+                if (MOVING) {
+                    get(stvx, vx);
+                    get(stvy, vy);
+                }
+            }
+            const int m = min(LEAF_POINTS, wn - l * LEAF_POINTS);
+            float4 leaf, vel = make_float4(0.f, 0.f, 0.f, 0.f);
+            make_leaf<MOVING>([&](int k) {
+                // past the end: the first point again
+                const bool on = k < m;
+                return make_float4(on ? x[k] : x[0], on ? y[k] : y[0], MOVING ? (on ? vx[k] : vx[0]) : 0.0f,
+                                   MOVING ? (on ? vy[k] : vy[0]) : 0.0f);
+            }, leaf, vel);
+            const int gl = w0 / LEAF_POINTS + l;
+            out.leaf[gl] = leaf;
+            if (MOVING) out.leaf_vel[gl] = vel;
+        }
+        __syncthreads();
+    }
+    for (int s = wid; s * SUPER_LEAVES < nleaf; s += SMALL_THREADS / WAVE) {
+        const int l = s * SUPER_LEAVES + lane;
+        const bool on = l < nleaf;
+        const float4 leaf = on ? out.leaf[l] : make_float4(0.f, 0.f, 0.f, 0.f);
+        const float4 vel = MOVING && on ? out.leaf_vel[l] : make_float4(0.f, 0.f, 0.f, 0.f);
+        const float4 node = make_super<MOVING>(on, leaf, vel);
+        if (lane == 0) out.super[s] = node;
+    }
+}
+
+// ------------------------------------------------------------ many workgroups
+// Cell counts cleared; the sample's range (workgroup 0).
+__global__ __launch_bounds__(1024) void k_points_init(PointIn in, PointWork w, bool moving) {
+    for (int c = blockIdx.x * 1024 + threadIdx.x; c < (1 << LARGE_CELL_BITS); c += gridDim.x * 1024) w.cells[c] = 0;
+    if (blockIdx.x != 0) return;
+    const int bits = moving ? LARGE_CELL_BITS - 1 : LARGE_CELL_BITS;
+    const int wid = threadIdx.x / WAVE;
+    if (wid > 1) return;
+    const float2 r = sample_range(in, wid == 0 ? in.x : in.y, 1 << (wid == 0 ? (bits + 1) / 2 : bits / 2));
+    if ((threadIdx.x & (WAVE - 1)) == 0) {
+        w.grid[wid] = r.x;
+        w.grid[2 + wid] = r.y;
+    }
+}
+
+// Cell and rank of every valid point ((~0, ~0) for the others).
+__global__ __launch_bounds__(256) void k_points_count(PointIn in, PointWork w, bool moving) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= in.n) return;
+    uint2 cr = make_uint2(~0u, ~0u);
+    if (point_ok(in, i)) {
+        const Grid G{w.grid[0], w.grid[1], w.grid[2], w.grid[3]};
+        cr.x = cell_of(G, LARGE_CELL_BITS, moving, moving && point_moves(in, i), in.x[i], in.y[i]);
+        cr.y = atomicAdd(&w.cells[cr.x], 1u);
+    }
+    w.cell_rank[i] = cr;
+}
+
+// Exclusive sums of 1024 cells per workgroup; totals to block_sums.
+__global__ __launch_bounds__(1024) void k_points_scan(PointWork w) {
+    __shared__ int sh[16];
+    const int t = threadIdx.x, lane = t & (WAVE - 1), wid = t / WAVE;
+    const int c = blockIdx.x * 1024 + t;
+    const int v = static_cast<int>(w.cells[c]);
+    const int incl = wave_scan(v);
+    if (lane == WAVE - 1) sh[wid] = incl;
+    __syncthreads();
+    int base = 0, total = 0;
+    for (int k = 0; k < 16; ++k) {
+        base += k < wid ? sh[k] : 0;
+        total += sh[k];
+    }
+    w.cells[c] = static_cast<unsigned>(base + incl - v);
+    if (t == 0) w.block_sums[blockIdx.x] = total;
+}
+
+// Exclusive sums of the workgroup totals, and the valid count.
+__global__ __launch_bounds__(256) void k_points_scan_top(PointWork w, int* n_valid) {
+    __shared__ int sh[4];
+    static_assert((1 << LARGE_CELL_BITS) / 1024 == 256, "one total per thread");
+    const int t = threadIdx.x, lane = t & (WAVE - 1), wid = t / WAVE;
+    const int v = w.block_sums[t];
+    const int incl = wave_scan(v);
+    if (lane == WAVE - 1) sh[wid] = incl;
+    __syncthreads();
+    int base = 0, total = 0;
+    for (int k = 0; k < 4; ++k) {
+        base += k < wid ? sh[k] : 0;
+        total += sh[k];
+    }
+    w.block_sums[t] = base + incl - v;
+    if (t == 0) *n_valid = total;
+}
+
+// Positions of the valid points from their cell's sum and rank.
+__global__ __launch_bounds__(256) void k_points_positions(int n, PointWork w) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= n) return;
+    const uint2 cr = w.cell_rank[i];
+    w.positions[i] = cr.x == ~0u ? ~0u : w.cells[cr.x] + cr.y + static_cast<unsigned>(w.block_sums[cr.x >> 10]);
+}
+
+// Every valid point to its position.
+__global__ __launch_bounds__(256) void k_points_place(PointIn in, PointSet out,
+                                                      const unsigned* __restrict__ positions, bool moving) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= in.n) return;
+    const unsigned pos = positions[i];
+    const float x = in.x[i], y = in.y[i];
+    const float vx = in.vx ? in.vx[i] : 0.0f, vy = in.vy ? in.vy[i] : 0.0f;
+    if (pos == ~0u) return;
+    out.x[pos] = x;
+    out.y[pos] = y;
+    if (moving) {
+        out.vx[pos] = vx;
+        out.vy[pos] = vy;
+        out.xyv[pos] = make_float4(x, y, vx, vy);
+    } else {
+        out.xy[pos] = make_float2(x, y);
+    }
+    out.idx[pos] = i;
+}
+
+// One wave per super node: lane = leaf.
+template <bool MOVING>
+__global__ __launch_bounds__(WAVE) void k_points_nodes(PointSet out) {
+    const int nv = *out.n_valid;
+    const int nleaf = (nv + LEAF_POINTS - 1) / LEAF_POINTS;
+    if (static_cast<int>(blockIdx.x) * SUPER_LEAVES >= nleaf) return;
+    const int l = blockIdx.x * SUPER_LEAVES + threadIdx.x;
+    const bool on = l < nleaf;
+    float4 leaf = make_float4(0.f, 0.f, 0.f, 0.f), vel = leaf;
+    if (on) {
+        const int j0 = l * LEAF_POINTS;
+        make_leaf<MOVING>([&](int k) {
+            const int j = min(j0 + k, nv - 1);
+            if (MOVING) return out.xyv[j];
+            const float2 o = out.xy[j];
+            return make_float4(o.x, o.y, 0.0f, 0.0f);
+        }, leaf, vel);
+        out.leaf[l] = leaf;
+        if (MOVING) out.leaf_vel[l] = vel;
+    }
+    const float4 node = make_super<MOVING>(on, leaf, vel);
+    if (threadIdx.x == 0) out.super[blockIdx.x] = node;
+}
+
+// Cells of the one-workgroup grid: about eight per point, since points
+// crowd on walls (at least 256, the multiple of 16 cells per wave that the
+// scan needs; at most 2^16, 128 KB).
+int small_cell_bits(int n) {
+    int b = 8;
+    while (b < 16 && (1 << b) < 8 * n) ++b;
+    return b;
+}
+
+size_t small_lds(int n, int cell_bits, bool moving) {
+    const size_t hist = (sizeof(unsigned short) << cell_bits) + (sizeof(unsigned short) << cell_bits) / 8;
+    if (n > 8 * SMALL_THREADS) return hist;
+    const int W = moving ? WINDOW / 2 : WINDOW;
+    const size_t W8 = static_cast<size_t>(((n < W ? n : W) + 7) & ~7);
+    const size_t stage = W8 * ((moving ? 4 : 2) * sizeof(float) + sizeof(unsigned short));
+    return ((hist > stage ? hist : stage) + 15) & ~static_cast<size_t>(15);
+}
+
+template <bool MOVING>
+hipError_t launch_nodes(const PointSet& out, int n, hipStream_t s) {
+    const int nsuper = (n + LEAF_POINTS * SUPER_LEAVES - 1) / (LEAF_POINTS * SUPER_LEAVES);
+    hipLaunchKernelGGL((k_points_nodes<MOVING>), dim3(nsuper), dim3(WAVE), 0, s, out);
+    return hipGetLastError();
+}
+
+template <int PT, bool MOVING>
+hipError_t launch_small(const PointIn& in, const PointSet& out, unsigned* positions, hipStream_t s) {
+    const int bits = small_cell_bits(in.n);
+    const size_t lds = small_lds(in.n, bits, MOVING);
+    if (lds > 64 * 1024) {
+        // beyond the default limit of dynamic LDS (a property of the kernel, set again harmlessly)
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_points_small<PT, MOVING>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, 152 * 1024);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL((k_points_small<PT, MOVING>), dim3(1), dim3(SMALL_THREADS), lds, s, in, out, bits,
+                       positions);
+    if (PT > 8) {
+        hipLaunchKernelGGL(k_points_place, dim3((in.n + 255) / 256), dim3(256), 0, s, in, out, positions, MOVING);
+        return launch_nodes<MOVING>(out, in.n, s);
+    }
+    return hipGetLastError();
+}
+
+template <bool MOVING>
+hipError_t launch_small_m(const PointIn& in, const PointSet& out, unsigned* positions, hipStream_t s) {
+    const int pt = (in.n + SMALL_THREADS - 1) / SMALL_THREADS;
+    if (pt <= 4) return launch_small<4, MOVING>(in, out, positions, s);
+    if (pt <= 8) return launch_small<8, MOVING>(in, out, positions, s);
+    if (pt <= 16) return launch_small<16, MOVING>(in, out, positions, s);
+    return launch_small<32, MOVING>(in, out, positions, s);
+}
+
+}  // namespace
+
+size_t points_work_bytes(int n) {
+    if (n <= 8 * SMALL_THREADS) return 0;
+    const size_t positions = sizeof(unsigned) * static_cast<size_t>(n);
+    if (n <= POINTS_SMALL_MAX) return positions;
+    return positions + sizeof(uint2) * static_cast<size_t>(n) + sizeof(unsigned) * (1 << LARGE_CELL_BITS) +
+           sizeof(int) * 256 + sizeof(float) * 64;
+}
+
+hipError_t launch_points(const float* x, const float* y, const float* vx, const float* vy,
+                         const unsigned char* valid, int n, const PointSet& out, void* work, hipStream_t s) {
+    const PointIn in{x, y, vx, vy, valid, n};
+    const bool moving = vx || vy;
+    if (n <= POINTS_DIRECT_MAX) {
+        hipLaunchKernelGGL(k_points_direct, dim3(1), dim3(POINTS_DIRECT_MAX), 0, s, in, out, moving);
+        return hipGetLastError();
+    }
+    PointWork w;
+    char* p = static_cast<char*>(work);
+    w.cell_rank = reinterpret_cast<uint2*>(p);  // first: 8-byte aligned
+    if (n > POINTS_SMALL_MAX) p += sizeof(uint2) * static_cast<size_t>(n);
+    w.positions = reinterpret_cast<unsigned*>(p);
+    if (n <= POINTS_SMALL_MAX)
+        return moving ? launch_small_m<true>(in, out, w.positions, s) : launch_small_m<false>(in, out, w.positions, s);
+    p += sizeof(unsigned) * static_cast<size_t>(n);
+    w.cells = reinterpret_cast<unsigned*>(p);
+    p += sizeof(unsigned) * (1 << LARGE_CELL_BITS);
+    w.block_sums = reinterpret_cast<int*>(p);
+    p += sizeof(int) * 256;
+    w.grid = reinterpret_cast<float*>(p);
+    const dim3 g((n + 255) / 256), b(256);
+    hipLaunchKernelGGL(k_points_init, dim3(64), dim3(1024), 0, s, in, w, moving);
+    hipLaunchKernelGGL(k_points_count, g, b, 0, s, in, w, moving);
+    hipLaunchKernelGGL(k_points_scan, dim3((1 << LARGE_CELL_BITS) / 1024), dim3(1024), 0, s, w);
+    hipLaunchKernelGGL(k_points_scan_top, dim3(1), dim3(256), 0, s, w, out.n_valid);
+    hipLaunchKernelGGL(k_points_positions, g, b, 0, s, n, w);
+    hipLaunchKernelGGL(k_points_place, g, b, 0, s, in, out, w.positions, moving);
+    return moving ? launch_nodes<true>(out, n, s) : launch_nodes<false>(out, n, s);
+}
+
+}  // namespace emppi

@@ -1,104 +1,99 @@
 // Single-scene kernels of the fused rollout-frame transform + exact signed
-// distance + min over points stage, the point-wise signed-distance kernels,
-// and the obstacle-point compaction that implements the validity mask.
-// The per-lane work is in sdf_device.hpp (shared with the batched kernel).
-#include "sdf_device.hpp"
+// distance + min over points stage, the footprint's bound table and the
+// point-wise signed-distance kernels.  The search is in cull_device.hpp, the
+// exact evaluation in sdf_device.hpp (shared with the batched kernel).
+#include "cull_device.hpp"
 
 namespace emppi {
 
 namespace {
 
-// Grid: x over poses (one lane each), y over point chunks of `chunk` points.
-// Each chunk's minimum is merged into the pose's key with atomicMin.
-// Waves per SIMD the register budget is tuned for (512 VGPRs per lane).
-template <int BP>
-constexpr int poly_waves() { return BP <= 8 ? 6 : BP <= 16 ? 4 : BP <= 20 ? 3 : 2; }
-
-template <int BP, bool MOVING, bool ARGMIN>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(poly_waves<BP>())))
-void k_dmin_poly(const float4* __restrict__ poses, int npose,
-                                                   PoseTime pt, PointArgs pts, int chunk,
-                                                   const float2* __restrict__ verts,
-                                                   unsigned int* __restrict__ key,
-                                                   unsigned long long* __restrict__ key64) {
-    extern __shared__ __align__(16) float lds[];  // point tiles: 8- and 16-byte LDS accesses
-    const int g = blockIdx.x * blockDim.x + threadIdx.x;
-    const bool live = g < npose;
-    const float4 q = live ? poses[g] : make_float4(0.f, 0.f, 1.f, 0.f);
-    const float tau = MOVING ? pose_tau(pt, g) : 0.0f;
-    const int nv = *pts.n_valid;
-    const int c0 = blockIdx.y * chunk;
-    const int c1 = min(c0 + chunk, nv);
-    float best;
-    int besti;
-    dmin_poly_range<BP, MOVING, ARGMIN>(q, tau, pts, c0, c1, verts, lds, best, besti);
-    if (live) {
-        if (ARGMIN) {
-            const unsigned int idx = besti >= 0 ? static_cast<unsigned int>(pts.idx[besti]) : 0xFFFFFFFFu;
-            atomicMin(&key64[g], (static_cast<unsigned long long>(dkey(best)) << 32) | idx);
-        } else {
-            atomicMin(&key[g], dkey(best));
-        }
-    }
+// Grid: x over pose tiles (P poses per wave), a workgroup taking `tiles` of
+// them a grid apart, so that each has poses of several horizon steps (later
+// steps, being more spread, cost more); y over ranges of `supers` super
+// nodes; each range's minimum is merged into the pose's key with atomicMin.
+template <typename Eval, bool MOVING, bool ARGMIN>
+__global__ __launch_bounds__(CULL_WAVES * WAVE) __attribute__((amdgpu_waves_per_eu(Eval::WAVES)))
+void k_dmin(CullArgs A, int P, int tiles, int supers, const float2* __restrict__ verts,
+            const float4* __restrict__ rects, int nprim) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    const int per_tile = (blockDim.x / WAVE) * P;
+    const int s0 = blockIdx.y * supers;
+    cull_block<Eval, MOVING, ARGMIN>(A, verts, rects, nprim, blockIdx.x * per_tile, gridDim.x * per_tile, P, tiles, s0,
+                                     s0 + supers, lds);
 }
 
-// Polygons of more than 16 padded vertices: a group of L lanes per pose (a
-// pair up to 32 vertices, a quad above), each lane holding HB edges
-// (PolyPart); the group's first lane merges the pose's key.  Register
-// budget: 4 waves per SIMD for static points (at 16 edges per lane the
-// compiler then spills only in the set-up, not in the point loop), 3 for
-// moving points (whose point loop would spill at 4).
-template <int HB, int L, bool MOVING, bool ARGMIN>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MOVING ? 3 : 4)))
-void k_dmin_poly_part(const float4* __restrict__ poses, int npose, PoseTime pt, PointArgs pts,
-                      int chunk, const float2* __restrict__ verts, unsigned int* __restrict__ key,
-                      unsigned long long* __restrict__ key64) {
-    extern __shared__ __align__(16) float lds[];  // point tiles: 8- and 16-byte LDS accesses
-    const int g = static_cast<int>((blockIdx.x * blockDim.x + threadIdx.x) / L);
-    const bool live = g < npose;
-    const float4 q = live ? poses[g] : make_float4(0.f, 0.f, 1.f, 0.f);
-    const float tau = MOVING ? pose_tau(pt, g) : 0.0f;
-    const int nv = *pts.n_valid;
-    const int c0 = blockIdx.y * chunk;
-    const int c1 = min(c0 + chunk, nv);
-    float best;
-    int besti;
-    dmin_poly_part_range<HB, L, MOVING, ARGMIN>(q, tau, pts, c0, c1, verts, lds, best, besti);
-    if (live && (threadIdx.x & (L - 1)) == 0) {
-        if (ARGMIN) {
-            const unsigned int idx = besti >= 0 ? static_cast<unsigned int>(pts.idx[besti]) : 0xFFFFFFFFu;
-            atomicMin(&key64[g], (static_cast<unsigned long long>(dkey(best)) << 32) | idx);
-        } else {
-            atomicMin(&key[g], dkey(best));
+// Cells of a footprint's bound table (FootTable), one thread each.  r: a bit
+// more than half the cell's diagonal.  Polygon: the distance is linear in
+// the cell when the nearest edge's projection stays inside the edge and every
+// other edge is further from the centre by more than 2 r; cover: when the
+// nearest box's distance stays that of one face and every other box is
+// further by more than 2 r.
+__global__ __launch_bounds__(256) void k_foot_table(int kind, const FootTable* __restrict__ F,
+                                                    uint32_t* __restrict__ cells,
+                                                    const float4* __restrict__ ta,
+                                                    const float4* __restrict__ tb, int count) {
+    const int c = blockIdx.x * blockDim.x + threadIdx.x;
+    if (c >= F->nx * F->ny) return;
+    const float x = (static_cast<float>(c % F->nx) + 0.5f - F->ox) * F->dx;
+    const float y = (static_cast<float>(c / F->nx) + 0.5f - F->oy) * F->dy;
+    const float r = F->err_cell;
+    float d = INFINITY, second = INFINITY;  // nearest and next distance
+    float gx = 0.0f, gy = 0.0f;             // gradient while linear
+    if (kind == 0) {
+        float m2 = INFINITY, v = 0.0f;
+        bool odd = false, inside = false;
+        EdgeEval last = edge_eval(x, y, tb[count - 1].y, ta[count - 1].x, ta[count - 1].y,
+                                  ta[count - 1].z, ta[count - 1].w, tb[count - 1].x);
+        for (int k = 0; k < count; ++k) {
+            const float4 a = ta[k];
+            const float len = tb[k].x;
+            const EdgeEval e = edge_eval(x, y, tb[k].y, a.x, a.y, a.z, a.w, len);
+            odd ^= (last.above != e.above) & last.right;
+            last = e;
+            if (e.d2 < m2) {
+                second = m2;
+                m2 = e.d2;
+                const float u = __builtin_fmaf(x, a.x, __builtin_fmaf(y, a.y, a.z));
+                v = __builtin_fmaf(y, a.x, __builtin_fmaf(x, -a.y, a.w));
+                inside = u >= r && u <= len - r;
+                gx = -a.y;
+                gy = a.x;
+            } else {
+                second = fminf(second, e.d2);
+            }
         }
-    }
-}
-
-template <int RP, bool MOVING, bool ARGMIN>
-__global__ __launch_bounds__(256) void k_dmin_rect(const float4* __restrict__ poses, int npose,
-                                                   PoseTime pt, PointArgs pts, int chunk,
-                                                   const float4* __restrict__ rects,
-                                                   unsigned int* __restrict__ key,
-                                                   unsigned long long* __restrict__ key64) {
-    extern __shared__ __align__(16) float lds[];  // point tiles: 8- and 16-byte LDS accesses
-    const int g = blockIdx.x * blockDim.x + threadIdx.x;
-    const bool live = g < npose;
-    const float4 q = live ? poses[g] : make_float4(0.f, 0.f, 1.f, 0.f);
-    const float tau = MOVING ? pose_tau(pt, g) : 0.0f;
-    const int nv = *pts.n_valid;
-    const int c0 = blockIdx.y * chunk;
-    const int c1 = min(c0 + chunk, nv);
-    float best;
-    int besti;
-    dmin_rect_range<RP, MOVING, ARGMIN>(q, tau, pts, c0, c1, rects, lds, best, besti);
-    if (live) {
-        if (ARGMIN) {
-            const unsigned int idx = besti >= 0 ? static_cast<unsigned int>(pts.idx[besti]) : 0xFFFFFFFFu;
-            atomicMin(&key64[g], (static_cast<unsigned long long>(dkey(best)) << 32) | idx);
-        } else {
-            atomicMin(&key[g], dkey(best));
+        const float dist = __builtin_sqrtf(m2);
+        d = odd ? -dist : dist;
+        second = __builtin_sqrtf(second);
+        if (!(inside && dist > 1e-4f * r && second > dist + 2.0f * r)) {
+            gx = gy = 0.0f;
+        } else if ((v < 0.0f) != odd) {
+            gx = -gx;
+            gy = -gy;
         }
+    } else {
+        for (int k = 0; k < count; ++k) {
+            const float4 b = ta[k];
+            const float s = signed_sqrt(box_s(x, y, b));
+            if (s < d) {
+                second = d;
+                d = s;
+                const float ex = x - b.x, ey = y - b.y;
+                const float ax = fabsf(ex) - b.z, ay = fabsf(ey) - b.w;
+                const bool fx = fabsf(ex) > r && ay < -r && ax > ay + 2.0f * r;
+                const bool fy = fabsf(ey) > r && ax < -r && ay > ax + 2.0f * r;
+                gx = fx ? copysignf(1.0f, ex) : 0.0f;
+                gy = fy ? copysignf(1.0f, ey) : 0.0f;
+            } else {
+                second = fminf(second, s);
+            }
+        }
+        if (!(second > d + 2.0f * r)) gx = gy = 0.0f;
     }
+    const float v = fminf(fmaxf(floorf((d - F->base) / F->quantum), 0.0f), 65535.0f);
+    const int ix = static_cast<int>(rintf(gx * 127.0f)), iy = static_cast<int>(rintf(gy * 127.0f));
+    cells[c] = static_cast<uint32_t>(v) | (static_cast<uint32_t>(ix & 255) << 16) | (static_cast<uint32_t>(iy & 255) << 24);
 }
 
 __global__ void k_key_init(unsigned int* __restrict__ key, unsigned long long* __restrict__ key64,
@@ -168,110 +163,21 @@ __global__ __launch_bounds__(256) void k_sdf_rect_points(const float* __restrict
     out[i] = signed_sqrt(s);
 }
 
-// ---------------------------------------------------------------- compaction
-// Order-preserving stream compaction of the valid, finite points (one
-// workgroup of 1024 lanes sweeps the array; wave ballots give the offsets).
-__global__ __launch_bounds__(1024) void k_compact_points(
-    const float* __restrict__ x, const float* __restrict__ y, const float* __restrict__ vx,
-    const float* __restrict__ vy, const unsigned char* __restrict__ valid, int n,
-    float* __restrict__ ox, float* __restrict__ oy, float* __restrict__ ovx,
-    float* __restrict__ ovy, int* __restrict__ oidx, int* __restrict__ n_valid) {
-    __shared__ int wsum[16];
-    const int lane = threadIdx.x & (WAVE - 1), wid = threadIdx.x / WAVE;
-    const int nw = blockDim.x / WAVE;
-    int base = 0;
-    for (int i0 = 0; i0 < n; i0 += blockDim.x) {
-        const int i = i0 + threadIdx.x;
-        bool ok = false;
-        float a = 0.f, b = 0.f, c = 0.f, d = 0.f;
-        if (i < n) {
-            a = x[i];
-            b = y[i];
-            ok = isfinite(a) && isfinite(b);
-            if (vx) {
-                c = vx[i];
-                ok = ok && isfinite(c);
-            }
-            if (vy) {
-                d = vy[i];
-                ok = ok && isfinite(d);
-            }
-            if (valid) ok = ok && valid[i] != 0;
-        }
-        const uint64_t m = __ballot(ok);
-        const int pre = __popcll(m & ((1ull << lane) - 1ull));
-        if (lane == 0) wsum[wid] = __popcll(m);
-        __syncthreads();
-        int off = 0, tot = 0;
-        for (int w = 0; w < nw; ++w) {
-            off += (w < wid) ? wsum[w] : 0;
-            tot += wsum[w];
-        }
-        if (ok) {
-            const int o = base + off + pre;
-            ox[o] = a;
-            oy[o] = b;
-            if (ovx) ovx[o] = c;
-            if (ovy) ovy[o] = d;
-            oidx[o] = i;
-        }
-        base += tot;
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *n_valid = base;
-}
-
-template <int BP, bool MOVING, bool ARGMIN>
-hipError_t launch_poly_t(const DminLaunch& L, dim3 grid, size_t lds, hipStream_t s) {
-    hipLaunchKernelGGL((k_dmin_poly<BP, MOVING, ARGMIN>), grid, dim3(L.block), lds, s, L.poses,
-                       L.npose, L.pt, L.pts, L.chunk, L.verts, L.key, L.key64);
+template <typename Eval, bool MOVING, bool ARGMIN>
+hipError_t launch_cull_t(const DminLaunch& L, hipStream_t s) {
+    const int per_wg = L.waves * L.poses_per_wave * L.tiles;
+    const dim3 grid((L.npose + per_wg - 1) / per_wg, L.nchunk);
+    const CullArgs A{L.poses, L.npose, L.pt, L.pts, L.foot, L.key, L.key64};
+    hipLaunchKernelGGL((k_dmin<Eval, MOVING, ARGMIN>), grid, dim3(L.waves * WAVE),
+                       cull_lds_bytes(L.waves, MOVING, ARGMIN), s, A, L.poses_per_wave, L.tiles, L.supers,
+                       L.verts, L.rects, L.padded);
     return hipGetLastError();
 }
 
-template <int RP, bool MOVING, bool ARGMIN>
-hipError_t launch_rect_t(const DminLaunch& L, dim3 grid, size_t lds, hipStream_t s) {
-    hipLaunchKernelGGL((k_dmin_rect<RP, MOVING, ARGMIN>), grid, dim3(L.block), lds, s, L.poses,
-                       L.npose, L.pt, L.pts, L.chunk, L.rects, L.key, L.key64);
-    return hipGetLastError();
-}
-
-template <int HB, int L, bool MOVING, bool ARGMIN>
-hipError_t launch_part_t(const DminLaunch& D, dim3 grid, size_t lds, hipStream_t s) {
-    hipLaunchKernelGGL((k_dmin_poly_part<HB, L, MOVING, ARGMIN>), grid, dim3(D.block), lds, s,
-                       D.poses, D.npose, D.pt, D.pts, D.chunk, D.verts, D.key, D.key64);
-    return hipGetLastError();
-}
-
-template <int HB, int L>
-hipError_t launch_part(const DminLaunch& D, dim3 grid, size_t lds, hipStream_t s) {
-    // L lanes per pose
-    const dim3 gl((L * D.npose + D.block - 1) / D.block, grid.y);
-    if (D.pts.vx) return D.argmin ? launch_part_t<HB, L, true, true>(D, gl, lds, s)
-                                  : launch_part_t<HB, L, true, false>(D, gl, lds, s);
-    return D.argmin ? launch_part_t<HB, L, false, true>(D, gl, lds, s)
-                    : launch_part_t<HB, L, false, false>(D, gl, lds, s);
-}
-
-template <int P>
-hipError_t launch_poly(const DminLaunch& L, dim3 grid, size_t lds, hipStream_t s) {
-    if constexpr (P > 32) {
-        return launch_part<P / 4, 4>(L, grid, lds, s);
-    } else if constexpr (P > 16) {
-        return launch_part<P / 2, 2>(L, grid, lds, s);
-    } else {
-        if (L.pts.vx) return L.argmin ? launch_poly_t<P, true, true>(L, grid, lds, s)
-                                      : launch_poly_t<P, true, false>(L, grid, lds, s);
-        return L.argmin ? launch_poly_t<P, false, true>(L, grid, lds, s)
-                        : launch_poly_t<P, false, false>(L, grid, lds, s);
-    }
-}
-
-template <int P>
-hipError_t launch_rect(const DminLaunch& L, dim3 grid, size_t lds, hipStream_t s) {
-    if (L.pts.vx) return L.argmin ? launch_rect_t<P, true, true>(L, grid, lds, s)
-                                  : launch_rect_t<P, true, false>(L, grid, lds, s);
-    return L.argmin ? launch_rect_t<P, false, true>(L, grid, lds, s)
-                    : launch_rect_t<P, false, false>(L, grid, lds, s);
+template <typename Eval>
+hipError_t launch_cull(const DminLaunch& L, hipStream_t s) {
+    if (L.pts.vx) return L.argmin ? launch_cull_t<Eval, true, true>(L, s) : launch_cull_t<Eval, true, false>(L, s);
+    return L.argmin ? launch_cull_t<Eval, false, true>(L, s) : launch_cull_t<Eval, false, false>(L, s);
 }
 
 }  // namespace
@@ -293,35 +199,12 @@ int dmin_padded_count(int kind, int count) {
 }
 
 hipError_t launch_dmin(const DminLaunch& L, hipStream_t s) {
-    const dim3 grid((L.npose + L.block - 1) / L.block, L.nchunk);
-    const size_t lds = static_cast<size_t>(DMIN_TILE) * (L.pts.vx ? 16 : 8);
+    if (L.every) return launch_dmin_every(L, s);
     if (L.kind == 0) {
-        switch (L.padded) {
-#define EMPPI_CASE(P) \
-    case P: return launch_poly<P>(L, grid, lds, s);
-            EMPPI_CASE(3) EMPPI_CASE(4) EMPPI_CASE(5) EMPPI_CASE(6) EMPPI_CASE(7) EMPPI_CASE(8)
-            EMPPI_CASE(9) EMPPI_CASE(10) EMPPI_CASE(11) EMPPI_CASE(12) EMPPI_CASE(13)
-            EMPPI_CASE(14) EMPPI_CASE(15) EMPPI_CASE(16) EMPPI_CASE(18) EMPPI_CASE(20)
-            EMPPI_CASE(22) EMPPI_CASE(24) EMPPI_CASE(26) EMPPI_CASE(28) EMPPI_CASE(30)
-            EMPPI_CASE(32) EMPPI_CASE(36) EMPPI_CASE(40) EMPPI_CASE(44) EMPPI_CASE(48)
-            EMPPI_CASE(52) EMPPI_CASE(56) EMPPI_CASE(60) EMPPI_CASE(64)
-#undef EMPPI_CASE
-        default: return hipErrorInvalidValue;
-        }
+        if (L.padded <= 16) return launch_cull<EvalPoly<1>>(L, s);
+        return L.padded <= 32 ? launch_cull<EvalPoly<2>>(L, s) : launch_cull<EvalPoly<4>>(L, s);
     }
-    switch (L.padded) {
-    case 1: return launch_rect<1>(L, grid, lds, s);
-    case 2: return launch_rect<2>(L, grid, lds, s);
-    case 3: return launch_rect<3>(L, grid, lds, s);
-    case 4: return launch_rect<4>(L, grid, lds, s);
-    case 6: return launch_rect<6>(L, grid, lds, s);
-    case 8: return launch_rect<8>(L, grid, lds, s);
-    case 12: return launch_rect<12>(L, grid, lds, s);
-    case 16: return launch_rect<16>(L, grid, lds, s);
-    case 24: return launch_rect<24>(L, grid, lds, s);
-    case 32: return launch_rect<32>(L, grid, lds, s);
-    default: return hipErrorInvalidValue;
-    }
+    return L.padded <= 16 ? launch_cull<EvalRect<1>>(L, s) : launch_cull<EvalRect<2>>(L, s);
 }
 
 hipError_t launch_key_init(unsigned int* key, unsigned long long* key64, int n, hipStream_t s) {
@@ -351,11 +234,10 @@ hipError_t launch_sdf_points(int kind, const float* px, const float* py, int n,
     return hipGetLastError();
 }
 
-hipError_t launch_compact_points(const float* x, const float* y, const float* vx, const float* vy,
-                                 const unsigned char* valid, int n, float* ox, float* oy,
-                                 float* ovx, float* ovy, int* oidx, int* n_valid, hipStream_t s) {
-    hipLaunchKernelGGL(k_compact_points, dim3(1), dim3(1024), 0, s, x, y, vx, vy, valid, n, ox, oy,
-                       ovx, ovy, oidx, n_valid);
+hipError_t launch_foot_table(int kind, FootTable* table, const float4* tab_a, const float4* tab_b,
+                             int count, hipStream_t s) {
+    hipLaunchKernelGGL(k_foot_table, dim3(FOOT_CELLS / 256), dim3(256), 0, s, kind, table,
+                       reinterpret_cast<uint32_t*>(table + 1), tab_a, tab_b, count);
     return hipGetLastError();
 }
 

@@ -277,7 +277,7 @@ struct PolyFrame {
     }
 };
 
-// Part of a footprint of L HB (padded) vertices for L = 2 or 4 consecutive
+// Part of a footprint of L HB (padded) vertices for L = 2, 4 or 16 consecutive
 // lanes that share one pose: lane j of the group holds edges
 // [j HB, (j + 1) HB), rotated exactly as in PolyFrame, and the y of the
 // vertex closing its last edge.  Splitting the per-lane registers lets large
@@ -286,7 +286,7 @@ struct PolyFrame {
 // the result is the same bits as one lane holding every edge).
 template <int HB, int L>
 struct PolyPart {
-    static_assert(L == 2 || L == 4, "lane groups of 2 or 4");
+    static_assert(L == 2 || L == 4 || L == 16, "lane groups of 2, 4 or 16");
     float Y[HB], EX[HB], EY[HB], NC[HB], CV[HB], LN[HB];
     float Yend;
 
