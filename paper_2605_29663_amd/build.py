@@ -10,7 +10,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libexact_mppi.so")
 BUILD = os.path.join(HERE, "_build")
-SOURCES = ["capi.hip", "capi_batch.hip", "capi_mlp.hip", "kernels_sdf.hip", "kernels_sdf_every.hip", "kernels_points.hip", "kernels_step.hip",
+SOURCES = ["capi.hip", "capi_batch.hip", "capi_mlp.hip", "kernels_sdf.hip", "kernels_sdf_every.hip", "kernels_search_batch.hip",
+           "kernels_points.hip", "kernels_step.hip",
            "kernels_batch.hip", "kernels_mlp.hip", "capi_cloud.hip", "kernels_cloud.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

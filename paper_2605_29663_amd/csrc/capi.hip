@@ -37,13 +37,15 @@ constexpr int SCRATCH_MAX_DEVICES = 64;
 std::mutex g_scratch_mu;
 void* g_scratch_ptr[SCRATCH_MAX_DEVICES] = {};
 
-// Device address of `scratch` on the current device `device`, looked up once.
+// Device address of `scratch` on the current device `device`, looked up once
+// (with what else is set up once per device).
 hipError_t scratch_lookup(int device) {
     if (device < 0 || device >= SCRATCH_MAX_DEVICES) return hipErrorInvalidDevice;
     std::lock_guard<std::mutex> lk(g_scratch_mu);
     if (g_scratch_ptr[device]) return hipSuccess;
     void* p = nullptr;
-    const hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
+    hipError_t e = points_setup();
+    if (e == hipSuccess) e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
     if (e == hipSuccess) g_scratch_ptr[device] = p;
     return e;
 }

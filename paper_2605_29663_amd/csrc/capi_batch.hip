@@ -26,9 +26,11 @@ struct mppi_batch_s {
     int resident[2][DMIN_CLASSES] = {};  // resident workgroups of each persistent launch
     std::vector<SceneBufs> bufs;
     std::vector<SceneDmin> sdm;     // [pass][scene]
-    std::vector<DminItem> items[2][DMIN_CLASSES];  // [pass][register class]
+    std::vector<DminItem> items[2][DMIN_CLASSES];  // [pass][register class], every-point scenes
+    std::vector<SearchItem> search[2][SEARCH_CLASSES];  // [pass][kernel variant], the other scenes
+    std::vector<int> search_order[2];                   // variants with items, most work first
     std::vector<int2> blk_roll, blk_upd;
-    DevBuf arena, d_steps, d_bufs, d_sdm, d_items[2][DMIN_CLASSES], d_blk_roll, d_blk_upd, d_counters, d_out;
+    DevBuf arena, d_steps, d_bufs, d_sdm, d_items[2][DMIN_CLASSES], d_search[2][SEARCH_CLASSES], d_blk_roll, d_blk_upd, d_counters, d_out;
     SceneStep* h_steps = nullptr;   // pinned
     float* h_out = nullptr;         // pinned
     // graph
@@ -100,6 +102,8 @@ void snapshot(mppi_batch b) {
         b->snap_ptr.push_back(c->pvx.p);
         b->snap_ptr.push_back(c->poly_verts.p);
         b->snap_ptr.push_back(c->rects.p);
+        for (const DevBuf* d : {&c->pxy, &c->leaf, &c->leaf_vel, &c->super, &c->poly_foot, &c->rect_foot})
+            b->snap_ptr.push_back(d->p);
     }
 }
 
@@ -112,6 +116,8 @@ bool snapshot_matches(mppi_batch b) {
         if (b->snap_ptr[m++] != c->px.p || b->snap_ptr[m++] != c->pvx.p ||
             b->snap_ptr[m++] != c->poly_verts.p || b->snap_ptr[m++] != c->rects.p)
             return false;
+        for (const DevBuf* d : {&c->pxy, &c->leaf, &c->leaf_vel, &c->super, &c->poly_foot, &c->rect_foot})
+            if (b->snap_ptr[m++] != d->p) return false;
     }
     return true;
 }
@@ -132,6 +138,8 @@ int plan(mppi_batch b, double work_target) {
     b->sdm.assign(2 * n, SceneDmin{});
     for (auto& p : b->items)
         for (auto& v : p) v.clear();
+    for (auto& p : b->search)
+        for (auto& v : p) v.clear();
     b->blk_roll.clear();
     b->blk_upd.clear();
     int cus = 0;
@@ -148,6 +156,11 @@ int plan(mppi_batch b, double work_target) {
         DminItem it;
     };
     std::vector<Cost> q[2][DMIN_CLASSES];
+    struct SearchCost {
+        double c;
+        SearchItem it;
+    };
+    std::vector<SearchCost> sq[2][SEARCH_CLASSES];
     // arena layout
     std::vector<size_t> off(n * 9);
     size_t total = 0;
@@ -156,12 +169,14 @@ int plan(mppi_batch b, double work_target) {
     // items), shrunk for small batches so that the sampled-rollout pass
     // still has about two rounds of resident workgroups
     double total_pairs = 0.0;
+    long long search_poses = 0;
     int slots = 1, val_slots = 1;  // resident workgroups of the classes this batch uses
     for (int s = 0; s < n; ++s) {
         const mppi_params& P = b->prms[s];
         mppi_ctx c = b->scenes[s];
         const int padded = P.footprint_kind == 0 ? c->BP : c->RP;
         total_pairs += static_cast<double>(b->args[s].Kpad) * P.T * std::max(c->n_points, 0) * padded;
+        if (!dmin_every(padded, c->n_points)) search_poses += static_cast<long long>(b->args[s].Kpad) * P.T;
         const int cls = dmin_class(P.footprint_kind, padded);
         slots = std::max(slots, b->resident[0][cls]);
         val_slots = std::max(val_slots, b->resident[1][cls]);
@@ -236,7 +251,30 @@ int plan(mppi_batch b, double work_target) {
             D.verts = c->poly_verts.as<float2>();
             D.rects = c->rects.as<float4>();
             D.key = pass == 0 ? B.key : B.key_nom;
+            D.foot = (kind == 0 ? c->poly_foot : c->rect_foot).as<FootTable>();
             if (pass == 1 && !P.validate) continue;
+            if (!dmin_every(padded, c->n_points)) {
+                // bounded search: the poses an item takes from the requested
+                // work per item (its pairs, as if every point were evaluated);
+                // by default so that the batch fills the chip's wave slots
+                // once, at most 512 (the footprint's table is then loaded once
+                // per 4 tiles).  Validation: one pose per wave.
+                const double pairs = static_cast<double>(std::max(c->n_points, 1)) * padded;
+                double want = static_cast<double>(search_poses) / (256.0 * 24.0) * SEARCH_WAVES;
+                if (work_target > 0.0) want = work_per_item / pairs;
+                const int n = pass == 1 ? SEARCH_WAVES
+                                        : static_cast<int>(std::min(512.0, std::max(want, 1.0 * SEARCH_WAVES)));
+                const int per_wave = (n + SEARCH_WAVES - 1) / SEARCH_WAVES;
+                const int tiles = (per_wave + DMIN_MAX_POSES - 1) / DMIN_MAX_POSES;
+                const int pw = (per_wave + tiles - 1) / tiles;
+                const int step = SEARCH_WAVES * pw * tiles;
+                auto& list = sq[pass][search_class(kind, padded, c->moving)];
+                for (int g0 = 0; g0 < D.npose; g0 += step)
+                    // later horizon steps are more spread and cost more
+                    list.push_back({std::min(step, D.npose - g0) * (1.0 + static_cast<double>(g0) / D.npose),
+                                    SearchItem{pass * b->n + s, g0, pw, tiles}});
+                continue;
+            }
             const int tile = (pass == 0 ? 256 : 128) / dmin_persistent_lanes_per_pose(cls);
             const int nck = pass == 0 ? nchunk[s] : nchunk_nom[s];
             for (int g0 = 0; g0 < D.npose; g0 += tile) {
@@ -289,6 +327,21 @@ int plan(mppi_batch b, double work_target) {
             return class_work[pass][x] > class_work[pass][y];
         });
     }
+    for (int pass = 0; pass < 2; ++pass) {
+        double work[SEARCH_CLASSES] = {};
+        auto& o = b->search_order[pass];
+        o.clear();
+        for (int cls = 0; cls < SEARCH_CLASSES; ++cls) {
+            auto& v = sq[pass][cls];
+            std::stable_sort(v.begin(), v.end(), [](const SearchCost& x, const SearchCost& y) { return x.c > y.c; });
+            for (const auto& e : v) {
+                b->search[pass][cls].push_back(e.it);
+                work[cls] += e.c;
+            }
+            if (!v.empty()) o.push_back(cls);
+        }
+        std::stable_sort(o.begin(), o.end(), [&](int x, int y) { return work[x] > work[y]; });
+    }
     // upload tables
     BHIP(b, hipStreamSynchronize(b->stream));
     BHIP(b, b->d_bufs.ensure(sizeof(SceneBufs) * n));
@@ -308,6 +361,13 @@ int plan(mppi_batch b, double work_target) {
             if (!v.empty())
                 BHIP(b, hipMemcpy(b->d_items[pass][cls].p, v.data(), sizeof(DminItem) * v.size(),
                                   hipMemcpyHostToDevice));
+        }
+    for (int pass = 0; pass < 2; ++pass)
+        for (int cls = 0; cls < SEARCH_CLASSES; ++cls) {
+            const auto& v = b->search[pass][cls];
+            if (v.empty()) continue;
+            BHIP(b, b->d_search[pass][cls].ensure(sizeof(SearchItem) * v.size()));
+            BHIP(b, hipMemcpy(b->d_search[pass][cls].p, v.data(), sizeof(SearchItem) * v.size(), hipMemcpyHostToDevice));
         }
     snapshot(b);
     b->planned = true;
@@ -329,6 +389,9 @@ int persistent_grid(mppi_batch b, int pass, int cls, size_t n_items) {
 // one device: the classes' workgroups then share compute units from the
 // start instead of only in each class's tail.)
 int launch_dmin_pass(mppi_batch b, int pass) {
+    for (const int cls : b->search_order[pass])
+        BHIP(b, launch_search_batched(cls, b->d_sdm.as<SceneDmin>(), b->d_search[pass][cls].as<SearchItem>(),
+                                      static_cast<int>(b->search[pass][cls].size()), b->stream));
     for (const int cls : b->cls_order[pass]) {
         const auto& v = b->items[pass][cls];
         BHIP(b, launch_dmin_persistent(cls, persistent_block(pass), persistent_grid(b, pass, cls, v.size()),
@@ -495,6 +558,8 @@ int mppi_batch_destroy(mppi_batch b) {
         for (DevBuf* x : bufs) x->release();
         for (auto& pass : b->d_items)
             for (DevBuf& x : pass) x.release();
+        for (auto& pass : b->d_search)
+            for (DevBuf& x : pass) x.release();
         if (b->h_steps) (void)hipHostFree(b->h_steps);
         if (b->h_out) (void)hipHostFree(b->h_out);
         if (b->ev0) (void)hipEventDestroy(b->ev0);
@@ -657,6 +722,10 @@ int mppi_batch_info(mppi_batch b, long long* items_main, long long* items_valida
     for (int cls = 0; cls < DMIN_CLASSES; ++cls) {
         m += static_cast<long long>(b->items[0][cls].size());
         v += static_cast<long long>(b->items[1][cls].size());
+    }
+    for (int cls = 0; cls < SEARCH_CLASSES; ++cls) {
+        m += static_cast<long long>(b->search[0][cls].size());
+        v += static_cast<long long>(b->search[1][cls].size());
     }
     if (items_main) *items_main = m;
     if (items_validation) *items_validation = v;

@@ -285,7 +285,7 @@ inline void choose_tiles(int kind, int padded, int npose, int n_points, int& blo
 // workgroups takes them all: with a part of a second round, the chip waits
 // for few workgroups as long as for many.  block = poses per workgroup (0:
 // that rule).
-constexpr int DMIN_WAVES = 8;
+constexpr int DMIN_WAVES = emppi::SEARCH_WAVES;
 constexpr int DMIN_MAX_POSES = 16;  // per wave and tile
 inline void dmin_shape(int kind, int padded, int npose, int block, int& poses_per_wave, int& tiles) {
     const int waves = 256 * (kind == 0 && padded > 32 ? 16 : 24);

@@ -74,6 +74,7 @@ struct PointWork {
     float* grid;  // lo x, lo y, cells per metre x, y
 };
 size_t points_work_bytes(int n);
+hipError_t points_setup();  // once per device, before the first launch_points
 hipError_t launch_points(const float* x, const float* y, const float* vx, const float* vy,
                          const unsigned char* valid, int n, const PointSet& out, void* work, hipStream_t s);
 
@@ -268,8 +269,23 @@ struct SceneDmin {
     int kind, padded;
     const float2* verts;
     const float4* rects;
+    const FootTable* foot;
     unsigned int* key;
 };
+
+// One workgroup's share of the batched bounded search: `tiles` tiles of
+// SEARCH_WAVES P consecutive poses of SceneDmin sd from g0.
+struct SearchItem {
+    int sd, g0, P, tiles;
+};
+constexpr int SEARCH_WAVES = 8;  // waves per workgroup
+// Kernel variant of the search: evaluator (edges or boxes per lane) and
+// static or moving points.
+constexpr int SEARCH_CLASSES = 10;
+inline int search_class(int kind, int padded, bool moving) {
+    const int e = kind == 1 ? (padded <= 16 ? 3 : 4) : padded <= 16 ? 0 : padded <= 32 ? 1 : 2;
+    return 2 * e + (moving ? 1 : 0);
+}
 
 // One work item: pose tile [g0, g0 + blockDim) of SceneDmin sd against the
 // compacted points [c0, c1) (clipped to the valid count on the device).
@@ -298,6 +314,8 @@ hipError_t launch_rollout_batched(const SceneStep* steps, const SceneBufs* bufs,
                                   int nblk, hipStream_t s);
 hipError_t launch_dmin_persistent(int cls, int block, int grid, const SceneDmin* sds,
                                   const DminItem* items, int n_items, int* counter, hipStream_t s);
+hipError_t launch_search_batched(int cls, const SceneDmin* sds, const SearchItem* items, int n_items,
+                                 hipStream_t s);
 hipError_t launch_cost_batched(const SceneStep* steps, const SceneBufs* bufs, const int2* blk,
                                int nblk, hipStream_t s);
 hipError_t launch_update_batched(const SceneStep* steps, const SceneBufs* bufs, const int2* blk,

@@ -561,12 +561,6 @@ template <int PT, bool MOVING>
 hipError_t launch_small(const PointIn& in, const PointSet& out, unsigned* positions, hipStream_t s) {
     const int bits = small_cell_bits(in.n);
     const size_t lds = small_lds(in.n, bits, MOVING);
-    if (lds > 64 * 1024) {
-        // beyond the default limit of dynamic LDS (a property of the kernel, set again harmlessly)
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_points_small<PT, MOVING>),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, 152 * 1024);
-        if (e != hipSuccess) return e;
-    }
     hipLaunchKernelGGL((k_points_small<PT, MOVING>), dim3(1), dim3(SMALL_THREADS), lds, s, in, out, bits,
                        positions);
     if (PT > 8) {
@@ -581,11 +575,26 @@ hipError_t launch_small_m(const PointIn& in, const PointSet& out, unsigned* posi
     const int pt = (in.n + SMALL_THREADS - 1) / SMALL_THREADS;
     if (pt <= 4) return launch_small<4, MOVING>(in, out, positions, s);
     if (pt <= 8) return launch_small<8, MOVING>(in, out, positions, s);
-    if (pt <= 16) return launch_small<16, MOVING>(in, out, positions, s);
     return launch_small<32, MOVING>(in, out, positions, s);
 }
 
 }  // namespace
+
+// Dynamic LDS beyond the default limit, on the current device (set_points
+// would pay 14 us for it in each call).
+hipError_t points_setup() {
+    const void* k[] = {reinterpret_cast<const void*>(k_points_small<4, false>),
+                       reinterpret_cast<const void*>(k_points_small<8, false>),
+                       reinterpret_cast<const void*>(k_points_small<32, false>),
+                       reinterpret_cast<const void*>(k_points_small<4, true>),
+                       reinterpret_cast<const void*>(k_points_small<8, true>),
+                       reinterpret_cast<const void*>(k_points_small<32, true>)};
+    for (const void* f : k) {
+        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 152 * 1024);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
 
 size_t points_work_bytes(int n) {
     if (n <= 8 * SMALL_THREADS) return 0;
