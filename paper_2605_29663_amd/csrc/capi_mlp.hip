@@ -17,7 +17,9 @@ struct mppi_proposal_s {
     long long n_params = 0;
     long long off[6] = {0};  // W1, b1, W2, b2, W3, b3 in the flat parameter vector
     DevBuf w, g, m, v;       // fp32 master parameters, gradients, Adam moments
-    DevBuf w1b, w2b, w3b;    // bf16 weight copies
+    DevBuf w1t, w2t, w3t, w2b, w3b;    // bf16 weight copies (MlpWeights)
+    int ld_in = 0, ld_h = 0, ld_out = 0, ld_m = 0;  // padded rows of the bf16 matrices
+    DevBuf xt, a1t, a2t, doutt, dh2t, dh1t;  // bf16, transposed over the batch: [cols][ld_m]
     DevBuf xb, pre1, a1b, pre2, a2b, outb, dout, doutb, dh2, dh2b, dh1, dh1b, rowsq, loss;
     float* h_loss = nullptr;  // pinned
     long long t = 0;          // Adam step
@@ -48,45 +50,105 @@ int pfail(mppi_proposal p, int code, const char* fmt, ...) {
 
 float* W(mppi_proposal p, DevBuf& b, int k) { return b.as<float>() + p->off[k]; }
 
+MlpWeights weights(mppi_proposal p) {
+    MlpWeights mw{};
+    mw.in = p->in;
+    mw.H = p->H;
+    mw.out = p->out;
+    for (int k = 0; k < 6; ++k) mw.off[k] = static_cast<long>(p->off[k]);
+    mw.w1t = p->w1t.as<uint16_t>();
+    mw.w2t = p->w2t.as<uint16_t>();
+    mw.w3t = p->w3t.as<uint16_t>();
+    mw.w2 = p->w2b.as<uint16_t>();
+    mw.w3 = p->w3b.as<uint16_t>();
+    mw.ld_in = p->ld_in;
+    mw.ld_h = p->ld_h;
+    mw.ld_out = p->ld_out;
+    return mw;
+}
+
 int refresh_bf16(mppi_proposal p) {
-    PHIP(p, launch_f32_to_bf16(W(p, p->w, 0), p->w1b.as<uint16_t>(), (long)p->in * p->H, p->stream));
-    PHIP(p, launch_f32_to_bf16(W(p, p->w, 2), p->w2b.as<uint16_t>(), (long)p->H * p->H, p->stream));
-    PHIP(p, launch_f32_to_bf16(W(p, p->w, 4), p->w3b.as<uint16_t>(), (long)p->H * p->out, p->stream));
+    PHIP(p, launch_weights(p->w.as<float>(), static_cast<long>(p->n_params), weights(p), p->stream));
     return MPPI_OK;
 }
 
-GemmArgs gemm(int M, int N, int K, const void* A, long sam, long sak, const void* B, long sbk,
-              long sbn, float* C, void* Cb, long ldc, const float* bias, const float* aux, int epi) {
-    GemmArgs g;
+// C = A B^T of bf16 matrices with padded rows; the epilogue's fields are the
+// caller's.
+MlpJob product(int kind, int M, int N, int K, const DevBuf& A, int lda, const DevBuf& B, int ldb, float* C) {
+    MlpJob g{};
+    g.kind = kind;
     g.M = M;
     g.N = N;
     g.K = K;
-    g.A = static_cast<const uint16_t*>(A);
-    g.sam = sam;
-    g.sak = sak;
-    g.B = static_cast<const uint16_t*>(B);
-    g.sbk = sbk;
-    g.sbn = sbn;
+    g.A = A.as<uint16_t>();
+    g.lda = lda;
+    g.B = B.as<uint16_t>();
+    g.ldb = ldb;
     g.C = C;
-    g.Cb = static_cast<uint16_t*>(Cb);
-    g.ldc = ldc;
-    g.bias = bias;
-    g.aux = aux;
-    g.epi = epi;
     return g;
 }
 
-// Forward pass of M feature rows (device fp32, M x in) into p->outb (M x out).
-int forward(mppi_proposal p, const float* dfeat, int M) {
-    const int in = p->in, H = p->H, O = p->out;
-    PHIP(p, launch_to_bf16_padded(dfeat, M, in, in, p->xb.as<uint16_t>(), in, p->stream));
-    PHIP(p, launch_gemm(gemm(M, H, in, p->xb.p, in, 1, p->w1b.p, H, 1, p->pre1.as<float>(), p->a1b.p, H,
-                             W(p, p->w, 1), nullptr, EPI_BIAS_GELU), p->stream));
-    PHIP(p, launch_gemm(gemm(M, H, H, p->a1b.p, H, 1, p->w2b.p, H, 1, p->pre2.as<float>(), p->a2b.p, H,
-                             W(p, p->w, 3), nullptr, EPI_BIAS_GELU), p->stream));
-    PHIP(p, launch_gemm(gemm(M, O, H, p->a2b.p, H, 1, p->w3b.p, O, 1, p->outb.as<float>(), nullptr, O,
-                             W(p, p->w, 5), nullptr, EPI_BIAS), p->stream));
+MlpJob colsum(int M, int N, const float* d, float* out) {
+    MlpJob g{};
+    g.kind = JOB_COLSUM;
+    g.M = M;
+    g.N = N;
+    g.aux = d;
+    g.C = out;
+    return g;
+}
+
+int run_jobs(mppi_proposal p, std::initializer_list<MlpJob> list) {
+    MlpJobs j{};
+    for (const MlpJob& g : list) j.job[j.n++] = g;
+    PHIP(p, launch_mlp(j, p->stream));
     return MPPI_OK;
+}
+
+// Forward pass of M feature rows (device fp32, M x in) into p->outb (M x out),
+// and where asked for a copy of the output, the output as control sequences,
+// or (training) the transposed activations and the gradient of the loss.
+int forward(mppi_proposal p, const float* dfeat, int M, float* copy, float* dU, const float* dtarget) {
+    const int in = p->in, H = p->H, O = p->out;
+    const bool train = dtarget != nullptr;
+    MlpJob g = product(EPI_BIAS_GELU, M, H, in, p->xb, p->ld_in, p->w1t, p->ld_in, p->pre1.as<float>());
+    g.A32 = dfeat;
+    g.xb = p->xb.as<uint16_t>();
+    g.bias = W(p, p->w, 1);
+    g.Cb = p->a1b.as<uint16_t>();
+    g.ldcb = p->ld_h;
+    g.Ct = train ? p->a1t.as<uint16_t>() : nullptr;
+    g.ldt = p->ld_m;
+    if (int rc = run_jobs(p, {g})) return rc;
+    g = product(EPI_BIAS_GELU, M, H, H, p->a1b, p->ld_h, p->w2t, p->ld_h, p->pre2.as<float>());
+    g.bias = W(p, p->w, 3);
+    g.Cb = p->a2b.as<uint16_t>();
+    g.ldcb = p->ld_h;
+    g.Ct = train ? p->a2t.as<uint16_t>() : nullptr;
+    g.ldt = p->ld_m;
+    MlpJob xt{};
+    xt.kind = JOB_TRANSPOSE;
+    xt.M = M;
+    xt.N = in;
+    xt.aux = dfeat;
+    xt.Ct = p->xt.as<uint16_t>();
+    xt.ldt = p->ld_m;
+    if (int rc = train ? run_jobs(p, {g, xt}) : run_jobs(p, {g})) return rc;
+    g = product(EPI_BIAS, M, O, H, p->a2b, p->ld_h, p->w3t, p->ld_h, p->outb.as<float>());
+    g.bias = W(p, p->w, 5);
+    g.C2 = copy;
+    g.U = dU;
+    g.feat = dfeat;
+    g.F = p->F;
+    if (train) {
+        g.tgt = dtarget;
+        g.dout = p->dout.as<float>();
+        g.Cb = p->doutb.as<uint16_t>();
+        g.ldcb = p->ld_out;
+        g.Ct = p->doutt.as<uint16_t>();
+        g.ldt = p->ld_m;
+    }
+    return run_jobs(p, {g});
 }
 
 int check_batch(mppi_proposal p, int M) {
@@ -136,21 +198,30 @@ int proposal_create(mppi_proposal* out, int device, void* hip_stream, int T, int
     DevBuf* f32[] = {&p->w, &p->g, &p->m, &p->v};
     for (DevBuf* b : f32)
         if (e == hipSuccess) e = b->ensure(P);
-    if (e == hipSuccess) e = p->w1b.ensure(2 * sizes[0]);
-    if (e == hipSuccess) e = p->w2b.ensure(2 * sizes[2]);
-    if (e == hipSuccess) e = p->w3b.ensure(2 * sizes[4]);
-    if (e == hipSuccess) e = p->xb.ensure(2 * MB * p->in);
+    // odd multiples of 64 bytes: rows a power of two apart share few L2 channels
+    auto pad = [](int v) { return (((v + 31) / 32) | 1) * 32; };
+    p->ld_in = pad(p->in);
+    p->ld_h = pad(hidden);
+    p->ld_out = pad(p->out);
+    p->ld_m = pad(max_batch);
+    // bf16 matrices, padding and all zero
+    const size_t LI = p->ld_in, LH = p->ld_h, LO = p->ld_out, LM = p->ld_m;
+    const std::pair<DevBuf*, size_t> b16[] = {
+        {&p->w1t, hidden * LI}, {&p->w2t, hidden * LH}, {&p->w3t, p->out * LH}, {&p->w2b, hidden * LH},
+        {&p->w3b, hidden * LO}, {&p->xb, MB * LI}, {&p->a1b, MB * LH}, {&p->a2b, MB * LH},
+        {&p->doutb, MB * LO}, {&p->dh2b, MB * LH}, {&p->dh1b, MB * LH}, {&p->xt, p->in * LM},
+        {&p->a1t, hidden * LM}, {&p->a2t, hidden * LM}, {&p->doutt, p->out * LM}, {&p->dh2t, hidden * LM},
+        {&p->dh1t, hidden * LM}};
+    for (const auto& x : b16) {
+        if (e == hipSuccess) e = x.first->ensure(2 * x.second);
+        if (e == hipSuccess) e = hipMemsetAsync(x.first->p, 0, 2 * x.second, p->stream);
+    }
     if (e == hipSuccess) e = p->pre1.ensure(4 * MB * hidden);
-    if (e == hipSuccess) e = p->a1b.ensure(2 * MB * hidden);
     if (e == hipSuccess) e = p->pre2.ensure(4 * MB * hidden);
-    if (e == hipSuccess) e = p->a2b.ensure(2 * MB * hidden);
     if (e == hipSuccess) e = p->outb.ensure(4 * MB * p->out);
     if (e == hipSuccess) e = p->dout.ensure(4 * MB * p->out);
-    if (e == hipSuccess) e = p->doutb.ensure(2 * MB * p->out);
     if (e == hipSuccess) e = p->dh2.ensure(4 * MB * hidden);
-    if (e == hipSuccess) e = p->dh2b.ensure(2 * MB * hidden);
     if (e == hipSuccess) e = p->dh1.ensure(4 * MB * hidden);
-    if (e == hipSuccess) e = p->dh1b.ensure(2 * MB * hidden);
     if (e == hipSuccess) e = p->rowsq.ensure(4 * MB);
     if (e == hipSuccess) e = p->loss.ensure(4);
     if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void**>(&p->h_loss), sizeof(float), 0);
@@ -173,7 +244,8 @@ int proposal_destroy(mppi_proposal p) {
     {
         DeviceGuard g(p->device);
         (void)hipStreamSynchronize(p->stream);
-        DevBuf* bufs[] = {&p->w, &p->g, &p->m, &p->v, &p->w1b, &p->w2b, &p->w3b, &p->xb, &p->pre1,
+        DevBuf* bufs[] = {&p->w, &p->g, &p->m, &p->v, &p->w1t, &p->w2t, &p->w3t, &p->w2b, &p->w3b, &p->xb,
+                          &p->xt, &p->a1t, &p->a2t, &p->doutt, &p->dh2t, &p->dh1t, &p->pre1,
                           &p->a1b, &p->pre2, &p->a2b, &p->outb, &p->dout, &p->doutb, &p->dh2,
                           &p->dh2b, &p->dh1, &p->dh1b, &p->rowsq, &p->loss};
         for (DevBuf* b : bufs) b->release();
@@ -245,18 +317,14 @@ int proposal_forward(mppi_proposal p, const float* dfeat, int M, float* dout) {
     if (!p || !dfeat || !dout) return MPPI_E_ARG;
     if (int rc = check_batch(p, M)) return rc;
     DeviceGuard g(p->device);
-    if (int rc = forward(p, dfeat, M)) return rc;
-    PHIP(p, hipMemcpyAsync(dout, p->outb.p, sizeof(float) * M * p->out, hipMemcpyDeviceToDevice, p->stream));
-    return MPPI_OK;
+    return forward(p, dfeat, M, dout, nullptr, nullptr);
 }
 
 int proposal_mean(mppi_proposal p, const float* dfeat, int M, float* dU) {
     if (!p || !dfeat || !dU) return MPPI_E_ARG;
     if (int rc = check_batch(p, M)) return rc;
     DeviceGuard g(p->device);
-    if (int rc = forward(p, dfeat, M)) return rc;
-    PHIP(p, launch_denorm(p->outb.as<float>(), dfeat, M, p->T, p->nu, p->F, dU, p->stream));
-    return MPPI_OK;
+    return forward(p, dfeat, M, nullptr, dU, nullptr);
 }
 
 int proposal_normalize(mppi_proposal p, const float* dU, const float* dfeat, int M, float* dtarget) {
@@ -282,25 +350,33 @@ int proposal_train_step(mppi_proposal p, const float* dfeat, const float* dtarge
     if (!(lr >= 0)) return pfail(p, MPPI_E_ARG, "lr must be >= 0");
     DeviceGuard g(p->device);
     const int in = p->in, H = p->H, O = p->out;
-    if (int rc = forward(p, dfeat, M)) return rc;
-    PHIP(p, launch_mse_grad(p->outb.as<float>(), dtarget, M, O, p->dout.as<float>(), p->doutb.as<uint16_t>(),
-                            p->rowsq.as<float>(), p->loss.as<float>(), p->stream));
-    // layer 3: dW3 = A2^T dOut, db3 = sum dOut, dH2 = (dOut W3^T) * gelu'(pre2)
-    PHIP(p, launch_gemm(gemm(H, O, M, p->a2b.p, 1, H, p->doutb.p, O, 1, W(p, p->g, 4), nullptr, O, nullptr,
-                             nullptr, EPI_STORE), p->stream));
-    PHIP(p, launch_colsum(p->dout.as<float>(), M, O, W(p, p->g, 5), p->stream));
-    PHIP(p, launch_gemm(gemm(M, H, O, p->doutb.p, O, 1, p->w3b.p, 1, O, p->dh2.as<float>(), p->dh2b.p, H,
-                             nullptr, p->pre2.as<float>(), EPI_GELU_GRAD), p->stream));
-    // layer 2
-    PHIP(p, launch_gemm(gemm(H, H, M, p->a1b.p, 1, H, p->dh2b.p, H, 1, W(p, p->g, 2), nullptr, H, nullptr,
-                             nullptr, EPI_STORE), p->stream));
-    PHIP(p, launch_colsum(p->dh2.as<float>(), M, H, W(p, p->g, 3), p->stream));
-    PHIP(p, launch_gemm(gemm(M, H, H, p->dh2b.p, H, 1, p->w2b.p, 1, H, p->dh1.as<float>(), p->dh1b.p, H,
-                             nullptr, p->pre1.as<float>(), EPI_GELU_GRAD), p->stream));
-    // layer 1
-    PHIP(p, launch_gemm(gemm(in, H, M, p->xb.p, 1, in, p->dh1b.p, H, 1, W(p, p->g, 0), nullptr, H, nullptr,
-                             nullptr, EPI_STORE), p->stream));
-    PHIP(p, launch_colsum(p->dh1.as<float>(), M, H, W(p, p->g, 1), p->stream));
+    if (int rc = forward(p, dfeat, M, nullptr, nullptr, dtarget)) return rc;
+    if (loss_out)
+        PHIP(p, launch_loss(p->outb.as<float>(), dtarget, M, O, p->rowsq.as<float>(), p->loss.as<float>(), p->stream));
+    // Gradients: dH2 = (dOut W3^T) * gelu'(pre2), dH1 = (dH2 W2^T) * gelu'(pre1),
+    // dW = A^T dY, db = sum dY.  Three launches: the chain dOut -> dH2 -> dH1 ->
+    // dW1 is three products long, and everything else runs beside its last two.
+    auto grad_h = [&](const DevBuf& dy, const DevBuf& w, int K, int ld, const DevBuf& pre, const DevBuf& d,
+                      const DevBuf& db, const DevBuf& dt) {
+        MlpJob g = product(EPI_GELU_GRAD, M, H, K, dy, ld, w, ld, d.as<float>());
+        g.aux = pre.as<float>();
+        g.Cb = db.as<uint16_t>();
+        g.ldcb = p->ld_h;
+        g.Ct = dt.as<uint16_t>();
+        g.ldt = p->ld_m;
+        return g;
+    };
+    auto grad_w = [&](int rows, int cols, const DevBuf& at, const DevBuf& dyt, int k) {
+        return product(EPI_STORE, rows, cols, M, at, p->ld_m, dyt, p->ld_m, W(p, p->g, k));
+    };
+    if (int rc = run_jobs(p, {grad_h(p->doutb, p->w3b, O, p->ld_out, p->pre2, p->dh2, p->dh2b, p->dh2t)})) return rc;
+    if (int rc = run_jobs(p, {grad_w(H, H, p->a1t, p->dh2t, 2), grad_w(H, O, p->a2t, p->doutt, 4),
+                              grad_h(p->dh2b, p->w2b, H, p->ld_h, p->pre1, p->dh1, p->dh1b, p->dh1t)}))
+        return rc;
+    if (int rc = run_jobs(p, {grad_w(in, H, p->xt, p->dh1t, 0), colsum(M, H, p->dh1.as<float>(), W(p, p->g, 1)),
+                              colsum(M, H, p->dh2.as<float>(), W(p, p->g, 3)),
+                              colsum(M, O, p->dout.as<float>(), W(p, p->g, 5))}))
+        return rc;
     // Adam
     p->t += 1;
     AdamArgs a;
@@ -313,8 +389,7 @@ int proposal_train_step(mppi_proposal p, const float* dfeat, const float* dtarge
     a.c1 = static_cast<float>(1.0 - std::pow(0.9, static_cast<double>(p->t)));
     a.c2 = static_cast<float>(1.0 - std::pow(0.999, static_cast<double>(p->t)));
     PHIP(p, launch_adam(p->w.as<float>(), p->g.as<float>(), p->m.as<float>(), p->v.as<float>(), p->n_params,
-                        a, p->stream));
-    if (int rc = refresh_bf16(p)) return rc;
+                        a, weights(p), p->stream));
     if (loss_out) {
         PHIP(p, hipMemcpyAsync(p->h_loss, p->loss.p, sizeof(float), hipMemcpyDeviceToHost, p->stream));
         PHIP(p, hipStreamSynchronize(p->stream));
@@ -336,9 +411,15 @@ int proposal_get_buffer(mppi_proposal p, int which, float* host, long long n) {
     }
     if (which >= 10 && which < 16) {
         DevBuf* b = b16[which - 10];
-        if (static_cast<size_t>(n) * 2 > b->cap) return pfail(p, MPPI_E_ARG, "n too large");
-        std::vector<uint16_t> tmp(n);
-        PHIP(p, hipMemcpyAsync(tmp.data(), b->p, 2 * n, hipMemcpyDeviceToHost, p->stream));
+        // stored with padded rows, returned without the padding
+        const int cols = which == 10 ? p->in : which == 13 ? p->out : p->H;
+        const int ld = which == 10 ? p->ld_in : which == 13 ? p->ld_out : p->ld_h;
+        if (n < 0 || n > static_cast<long long>(p->max_batch) * cols) return pfail(p, MPPI_E_ARG, "n too large");
+        const long long rows = (n + cols - 1) / cols;
+        std::vector<uint16_t> tmp(static_cast<size_t>(rows) * cols);
+        if (rows > 0)
+            PHIP(p, hipMemcpy2DAsync(tmp.data(), 2 * static_cast<size_t>(cols), b->p, 2 * static_cast<size_t>(ld),
+                                     2 * static_cast<size_t>(cols), rows, hipMemcpyDeviceToHost, p->stream));
         PHIP(p, hipStreamSynchronize(p->stream));
         for (long long i = 0; i < n; ++i) {
             const uint32_t u = static_cast<uint32_t>(tmp[i]) << 16;

@@ -30,6 +30,21 @@ __device__ __forceinline__ float gelu_grad(float x) {
            x * 0.39894228040143268f * expf(-0.5f * x * x);
 }
 
+// Normalised network output y at (state m, sequence entry k) -> control in
+// the actuator box: u = clamp(mid + half y, u_min, u_max) of its channel.  In
+// residual mode (res_scale > 0) the output is added to the previous
+// sequence's scaled value carried in the features: ys = feat_U + res_scale y.
+__device__ __forceinline__ float control_of(float y, const float* __restrict__ feat, int m, int k,
+                                            const FeatArgs& F) {
+    const int ch = k % F.nu;
+    const float ys = F.res_scale > 0.0f
+                         ? __builtin_fmaf(F.res_scale, y, feat[static_cast<size_t>(m) * F.in_dim + FEAT_BINS + 2 + k])
+                         : y;
+    const float mid = (F.umax[ch] + F.umin[ch]) * 0.5f;
+    const float half = (F.umax[ch] - F.umin[ch]) * 0.5f;
+    return fminf(fmaxf(mid + half * ys, F.umin[ch]), F.umax[ch]);
+}
+
 // ---------------------------------------------------------------- features
 // One workgroup per state.  Points go to the robot frame at q0 (rotation by
 // the single-precision sin/cos sequence), the bin is a pseudo-angle built from
@@ -97,103 +112,265 @@ __global__ __launch_bounds__(1024) void k_features(const float* __restrict__ px,
     }
 }
 
-// ---------------------------------------------------------------- conversion
-__global__ void k_to_bf16_padded(const float* __restrict__ src, int rows, int cols, int ld_src,
-                                 uint16_t* __restrict__ dst, int ld_dst) {
-    const int r = blockIdx.y, c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= rows || c >= ld_dst) return;
-    dst[static_cast<size_t>(r) * ld_dst + c] = c < cols ? to_bf16(src[static_cast<size_t>(r) * ld_src + c]) : 0;
-}
-
-// ---------------------------------------------------------------- GEMM
-// C[M x N] = A[M x K] * B[K x N] with general strides (bf16 operands):
-// A(m, k) = A[m * sam + k * sak], B(k, n) = B[k * sbk + n * sbn].
-// Workgroup tile 64 x 64 (4 waves in 2 x 2, each 32 x 32 = 2 x 2 blocks of
-// v_mfma_f32_16x16x32_bf16), K in steps of 32 through LDS, with the operands
-// stored k-contiguous ([row][k] and [col][k]) so each lane reads its 8
-// consecutive k values with one 16-byte load.  Lane l of a 16 x 16 x 32 MFMA
-// holds A rows l % 16, k = 8 (l / 16) .. +7, B columns l % 16 with the same k,
-// and D rows 4 (l / 16) .. +3 of column l % 16.
-constexpr int GT = 64, GK = 32, GKP = GK + 8;  // tile, k step, padded LDS row (bf16)
-
-__global__ __launch_bounds__(256) void k_gemm(GemmArgs g) {
-    __shared__ __attribute__((aligned(16))) uint16_t As[GT][GKP];
-    __shared__ __attribute__((aligned(16))) uint16_t Bs[GT][GKP];
-    const int m0 = blockIdx.y * GT, n0 = blockIdx.x * GT;
-    const int w = threadIdx.x / WAVE, l = threadIdx.x % WAVE;
-    const int wm = w / 2, wn = w % 2;
-    f32x4 acc[2][2];
-    for (int i = 0; i < 2; ++i)
-        for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int k0 = 0; k0 < g.K; k0 += GK) {
-        __syncthreads();
-        for (int e = threadIdx.x; e < GT * GK; e += blockDim.x) {
-            const int r = e / GK, k = e % GK;
-            const int m = m0 + r, n = n0 + r, kk = k0 + k;
-            As[r][k] = (m < g.M && kk < g.K) ? g.A[static_cast<size_t>(m) * g.sam + static_cast<size_t>(kk) * g.sak] : 0;
-            Bs[r][k] = (n < g.N && kk < g.K) ? g.B[static_cast<size_t>(kk) * g.sbk + static_cast<size_t>(n) * g.sbn] : 0;
-        }
-        __syncthreads();
-        bf16x8 a[2], b[2];
-        for (int i = 0; i < 2; ++i) {
-            const int row = wm * 32 + i * 16 + (l % 16);
-            a[i] = *reinterpret_cast<const bf16x8*>(&As[row][8 * (l / 16)]);
-        }
-        for (int j = 0; j < 2; ++j) {
-            const int col = wn * 32 + j * 16 + (l % 16);
-            b[j] = *reinterpret_cast<const bf16x8*>(&Bs[col][8 * (l / 16)]);
-        }
-        for (int i = 0; i < 2; ++i)
-            for (int j = 0; j < 2; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+// ---------------------------------------------------------------- products
+// C[M x N] = A[M x K] B[N x K]^T by waves of W x W blocks of
+// v_mfma_f32_16x16x32_bf16, each wave on its own: both operands are stored
+// k-contiguous (the producers write transposed copies where a product sums
+// over the batch), so a lane's 8 consecutive k values are one 16-byte load
+// from the L1 / L2 and no LDS staging, barrier or index arithmetic stands in
+// the loop.  The products of this network are small (1024 x 256 x 256 is 0.13
+// GFLOP) and bound by latency: what counts is one round of loads in flight
+// and a short chain of launches.  A training step of 1024 rows (in 146,
+// hidden 256, out 80) takes 7 launches; with 64 x 64 tiles staged element by
+// element and one launch per product it took 18 and 480 us.  Lane l of the
+// instruction holds A rows l % 16, k = 8 (l / 16) .. +7, B rows l % 16 with the
+// same k, and D rows 4 (l / 16) .. +3 of column l % 16; k ascends in steps of
+// 32, so every sum has one order whatever the tiles.
+template <int W>
+__device__ __forceinline__ void product_wave(const MlpJob& g, int tm, int tn) {
+    const int l = threadIdx.x & (WAVE - 1), r = l & 15, kq = (l >> 4) * 8;
+    const int m0 = tm * 16 * W, n0 = tn * 16 * W;
+    f32x4 acc[W][W];
+#pragma unroll
+    for (int i = 0; i < W; ++i)
+#pragma unroll
+        for (int j = 0; j < W; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // rows past the end read the last row (their results are not stored)
+    const uint16_t* pb[W];
+#pragma unroll
+    for (int j = 0; j < W; ++j) pb[j] = g.B + static_cast<size_t>(min(n0 + 16 * j + r, g.N - 1)) * g.ldb + kq;
+    // what the epilogue reads, on its way before the operands
+    float ext[W][W][4], bias[W];
+    const float* side = g.kind == EPI_GELU_GRAD ? g.aux : g.tgt;
+#pragma unroll
+    for (int j = 0; j < W; ++j) {
+        const int n = min(n0 + 16 * j + r, g.N - 1);
+        bias[j] = g.bias ? g.bias[n] : 0.f;
+        if (side)
+#pragma unroll
+            for (int i = 0; i < W; ++i)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const int m = min(m0 + 16 * i + 4 * (l >> 4) + t, g.M - 1);
+                    ext[i][j][t] = side[static_cast<size_t>(m) * g.N + n];
+                }
     }
-    for (int i = 0; i < 2; ++i)
-        for (int j = 0; j < 2; ++j)
+    // S steps are loaded as one round and consumed while the next round is on
+    // its way; steps past K load the last one and are skipped
+    constexpr int S = 8 / W;
+    bf16x8 a[2][S][W], b[2][S][W];
+    const int kend = (g.K + 31) & ~31;
+    auto consume = [&](int buf, int k0) {
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            if (k0 + 32 * s >= kend) break;
+#pragma unroll
+            for (int i = 0; i < W; ++i)
+#pragma unroll
+                for (int j = 0; j < W; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[buf][s][i], b[buf][s][j], acc[i][j], 0, 0, 0);
+        }
+    };
+    if (g.A32) {
+        const bool store = tn == 0;
+        for (int k0 = 0; k0 < kend; k0 += 32 * S) {
+            float x[S][W][8];
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+                const int k = min(k0 + 32 * s, kend - 32);
+#pragma unroll
+                for (int i = 0; i < W; ++i) {
+                    const float* pa = g.A32 + static_cast<size_t>(min(m0 + 16 * i + r, g.M - 1)) * g.K;
+                    if (k + 32 <= g.K) {
+                        __builtin_memcpy(x[s][i], pa + k + kq, 32);  // two 16-byte loads, 4-byte aligned
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) x[s][i][e] = pa[min(k + kq + e, g.K - 1)];
+                    }
+                }
+#pragma unroll
+                for (int j = 0; j < W; ++j) b[0][s][j] = *reinterpret_cast<const bf16x8*>(pb[j] + k);
+            }
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+                const int k = k0 + 32 * s + kq;
+                if (k0 + 32 * s >= kend) break;
+#pragma unroll
+                for (int i = 0; i < W; ++i) {
+                    const int m = m0 + 16 * i + r;
+                    union {
+                        uint16_t h[8];
+                        bf16x8 v;
+                        uint4 q;
+                    } u;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) u.h[e] = k + e < g.K ? to_bf16(x[s][i][e]) : 0;
+                    a[0][s][i] = u.v;
+                    if (store && m < g.M) *reinterpret_cast<uint4*>(g.xb + static_cast<size_t>(m) * g.lda + k) = u.q;
+                }
+            }
+            consume(0, k0);
+        }
+    } else {
+        const uint16_t* pa[W];
+#pragma unroll
+        for (int i = 0; i < W; ++i) pa[i] = g.A + static_cast<size_t>(min(m0 + 16 * i + r, g.M - 1)) * g.lda + kq;
+        auto fetch = [&](int buf, int k0) {
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+                const int k = min(k0 + 32 * s, kend - 32);
+#pragma unroll
+                for (int i = 0; i < W; ++i) a[buf][s][i] = *reinterpret_cast<const bf16x8*>(pa[i] + k);
+#pragma unroll
+                for (int j = 0; j < W; ++j) b[buf][s][j] = *reinterpret_cast<const bf16x8*>(pb[j] + k);
+            }
+        };
+        fetch(0, 0);
+        for (int k0 = 0; k0 < kend; k0 += 64 * S) {
+            if (k0 + 32 * S < kend) fetch(1, k0 + 32 * S);
+            consume(0, k0);
+            if (k0 + 32 * S >= kend) break;
+            if (k0 + 64 * S < kend) fetch(0, k0 + 64 * S);
+            consume(1, k0 + 32 * S);
+        }
+    }
+    const float scale = 2.0f / (static_cast<float>(g.M) * static_cast<float>(g.N));
+#pragma unroll
+    for (int i = 0; i < W; ++i)
+#pragma unroll
+        for (int j = 0; j < W; ++j) {
+            const int n = n0 + 16 * j + r, mq = m0 + 16 * i + 4 * (l >> 4);
+            if (n >= g.N) continue;
+            uint16_t h[4] = {0, 0, 0, 0};
+#pragma unroll
             for (int t = 0; t < 4; ++t) {
-                const int m = m0 + wm * 32 + i * 16 + 4 * (l / 16) + t;
-                const int n = n0 + wn * 32 + j * 16 + (l % 16);
-                if (m >= g.M || n >= g.N) continue;
-                const size_t o = static_cast<size_t>(m) * g.ldc + n;
-                float v = acc[i][j][t];
-                switch (g.epi) {
+                const int m = mq + t;
+                if (m >= g.M) continue;
+                const size_t o = static_cast<size_t>(m) * g.N + n;
+                const float v = acc[i][j][t];
+                switch (g.kind) {
                 case EPI_STORE:
                     g.C[o] = v;
                     break;
-                case EPI_BIAS:
-                    g.C[o] = v + g.bias[n];
+                case EPI_BIAS: {
+                    const float y = v + bias[j];
+                    g.C[o] = y;
+                    if (g.C2) g.C2[o] = y;
+                    if (g.tgt) {
+                        const float d = scale * (y - ext[i][j][t]);
+                        g.dout[o] = d;
+                        h[t] = to_bf16(d);
+                    }
+                    if (g.U) g.U[o] = control_of(y, g.feat, m, n, g.F);
                     break;
+                }
                 case EPI_BIAS_GELU: {
-                    const float pre = v + g.bias[n];
+                    const float pre = v + bias[j];
                     g.C[o] = pre;
-                    g.Cb[o] = to_bf16(gelu(pre));
+                    h[t] = to_bf16(gelu(pre));
                     break;
                 }
-                case EPI_GELU_GRAD: {
-                    const float d = v * gelu_grad(g.aux[o]);
+                default: {  // EPI_GELU_GRAD
+                    const float d = v * gelu_grad(ext[i][j][t]);
                     g.C[o] = d;
-                    g.Cb[o] = to_bf16(d);
+                    h[t] = to_bf16(d);
                     break;
                 }
-                default:
-                    break;
                 }
+                if (g.Cb) g.Cb[static_cast<size_t>(m) * g.ldcb + n] = h[t];
             }
+            // rows past M up to the transposed copy's padding are zero
+            if (g.Ct && mq < ((g.M + 31) & ~31)) {
+                const uint2 q = make_uint2(h[0] | (static_cast<unsigned>(h[1]) << 16),
+                                           h[2] | (static_cast<unsigned>(h[3]) << 16));
+                *reinterpret_cast<uint2*>(g.Ct + static_cast<size_t>(n) * g.ldt + mq) = q;
+            }
+        }
 }
 
-// ---------------------------------------------------------------- loss, bias grads
-// dOut = 2 (out - target) / (M n_out) (fp32 and bf16), per-row squared error.
-__global__ void k_mse_grad(const float* __restrict__ out, const float* __restrict__ tgt, int M,
-                           int n_out, float* __restrict__ dout, uint16_t* __restrict__ dout_b,
-                           float* __restrict__ row_sq) {
+// Column sums over the batch (bias gradients), fixed order: COLSUM_GROUPS row
+// groups; group g adds rows g, g + COLSUM_GROUPS, ... in turn, and the group
+// partials are added in group order.  A workgroup holds 16 columns x 16
+// groups.
+constexpr int COLSUM_GROUPS = 16;
+
+__device__ __forceinline__ void colsum_block(const MlpJob& g, int block) {
+    __shared__ float sh[COLSUM_GROUPS][16];
+    const int c = threadIdx.x & 15, grp = threadIdx.x >> 4;
+    const int n = block * 16 + c;
+    float s = 0.f;
+    if (n < g.N) {
+        constexpr int R = 32;  // loads in flight
+        int m = grp;
+        for (; m + (R - 1) * COLSUM_GROUPS < g.M; m += R * COLSUM_GROUPS) {
+            float x[R];
+#pragma unroll
+            for (int t = 0; t < R; ++t) x[t] = g.aux[static_cast<size_t>(m + t * COLSUM_GROUPS) * g.N + n];
+#pragma unroll
+            for (int t = 0; t < R; ++t) s += x[t];
+        }
+        for (; m < g.M; m += COLSUM_GROUPS) s += g.aux[static_cast<size_t>(m) * g.N + n];
+    }
+    sh[grp][c] = s;
+    __syncthreads();
+    if (grp == 0 && n < g.N) {
+        float t = sh[0][c];
+#pragma unroll
+        for (int k = 1; k < COLSUM_GROUPS; ++k) t += sh[k][c];
+        g.C[n] = t;
+    }
+}
+
+// Ct[N][ldt] = bf16(aux[M][N])^T, 32 x 32 a workgroup through the LDS.
+__device__ __forceinline__ void transpose_block(const MlpJob& g, int block) {
+    __shared__ uint16_t sh[32][33];
+    const int tm = block / g.tiles_n, m0 = tm * 32, n0 = (block - tm * g.tiles_n) * 32;
+    const int c = threadIdx.x & 31, r = threadIdx.x >> 5;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int m = m0 + r + 8 * i, n = n0 + c;
+        sh[r + 8 * i][c] = m < g.M && n < g.N ? to_bf16(g.aux[static_cast<size_t>(m) * g.N + n]) : 0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int n = n0 + r + 8 * i;
+        if (n < g.N) g.Ct[static_cast<size_t>(n) * g.ldt + m0 + c] = sh[c][r + 8 * i];
+    }
+}
+
+// The jobs of one launch side by side, each with a range of workgroups.
+__global__ __launch_bounds__(256) void k_mlp(MlpJobs jobs) {
+    int j = 0;
+    while (j + 1 < jobs.n && static_cast<int>(blockIdx.x) >= jobs.job[j + 1].block0) ++j;
+    const MlpJob& g = jobs.job[j];
+    const int block = static_cast<int>(blockIdx.x) - g.block0;
+    if (g.kind == JOB_COLSUM) {
+        colsum_block(g, block);
+        return;
+    }
+    if (g.kind == JOB_TRANSPOSE) {
+        transpose_block(g, block);
+        return;
+    }
+    const int t = block * 4 + static_cast<int>(threadIdx.x) / WAVE;
+    const int tm = t / g.tiles_n;
+    if (tm >= g.tiles_m) return;
+    if (g.W == 2)
+        product_wave<2>(g, tm, t - tm * g.tiles_n);
+    else
+        product_wave<1>(g, tm, t - tm * g.tiles_n);
+}
+
+// ---------------------------------------------------------------- loss
+// Squared error of each row of the output.
+__global__ void k_row_sq(const float* __restrict__ out, const float* __restrict__ tgt, int n_out,
+                         float* __restrict__ row_sq) {
     const int m = blockIdx.x;
     float acc = 0.f;
-    const float scale = 2.0f / (static_cast<float>(M) * static_cast<float>(n_out));
     for (int j = threadIdx.x; j < n_out; j += blockDim.x) {
         const size_t o = static_cast<size_t>(m) * n_out + j;
         const float e = out[o] - tgt[o];
-        const float d = scale * e;
-        dout[o] = d;
-        dout_b[o] = to_bf16(d);
         acc += e * e;
     }
     // fixed-order block sum (binary tree; blockDim.x is 256)
@@ -225,34 +402,27 @@ __global__ __launch_bounds__(LOSS_THREADS) void k_loss_sum(const float* __restri
     if (threadIdx.x == 0) *loss = sh[0] / (static_cast<float>(M) * static_cast<float>(n_out));
 }
 
-// Column sums over the batch (bias gradients), fixed order: a block holds
-// 64 columns (one per lane) and COLSUM_GROUPS row groups (one per wave);
-// group g adds rows g, g + COLSUM_GROUPS, ... in turn, and the group
-// partials are added in group order.
-constexpr int COLSUM_GROUPS = 16;
-
-__global__ __launch_bounds__(64 * COLSUM_GROUPS) void k_colsum(const float* __restrict__ d, int M, int N,
-                                                               float* __restrict__ out) {
-    __shared__ float sh[COLSUM_GROUPS][64];
-    const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
-    const int n = blockIdx.x * 64 + lane;
-    float s = 0.f;
-    if (n < N)
-        for (int m = g; m < M; m += COLSUM_GROUPS) s += d[static_cast<size_t>(m) * N + n];
-    sh[g][lane] = s;
-    __syncthreads();
-    if (g == 0 && n < N) {
-        float t = sh[0][lane];
-#pragma unroll
-        for (int k = 1; k < COLSUM_GROUPS; ++k) t += sh[k][lane];
-        out[n] = t;
+// ---------------------------------------------------------------- Adam
+// The bf16 copies of parameter i (matrices only; MlpWeights).
+__device__ __forceinline__ void store_weight(const MlpWeights& mw, long i, float w) {
+    const uint16_t h = to_bf16(w);
+    if (i < mw.off[1]) {
+        const int k = static_cast<int>(i) / mw.H, n = static_cast<int>(i) % mw.H;
+        mw.w1t[static_cast<size_t>(n) * mw.ld_in + k] = h;
+    } else if (i >= mw.off[2] && i < mw.off[3]) {
+        const int j = static_cast<int>(i - mw.off[2]), k = j / mw.H, n = j % mw.H;
+        mw.w2t[static_cast<size_t>(n) * mw.ld_h + k] = h;
+        mw.w2[static_cast<size_t>(k) * mw.ld_h + n] = h;
+    } else if (i >= mw.off[4] && i < mw.off[5]) {
+        const int j = static_cast<int>(i - mw.off[4]), k = j / mw.out, n = j % mw.out;
+        mw.w3t[static_cast<size_t>(n) * mw.ld_h + k] = h;
+        mw.w3[static_cast<size_t>(k) * mw.ld_out + n] = h;
     }
 }
 
-// ---------------------------------------------------------------- Adam
 // w -= lr * mhat / (sqrt(vhat) + eps), mhat = m / (1 - b1^t), vhat = v / (1 - b2^t).
 __global__ void k_adam(float* __restrict__ w, const float* __restrict__ grad, float* __restrict__ m,
-                       float* __restrict__ v, long n, AdamArgs a) {
+                       float* __restrict__ v, long n, AdamArgs a, MlpWeights mw) {
     const long i = static_cast<long>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const float g = grad[i];
@@ -261,30 +431,14 @@ __global__ void k_adam(float* __restrict__ w, const float* __restrict__ grad, fl
     m[i] = mi;
     v[i] = vi;
     const float mh = mi / a.c1, vh = vi / a.c2;
-    w[i] = w[i] - a.lr * mh / (sqrtf(vh) + a.eps);
+    const float wi = w[i] - a.lr * mh / (sqrtf(vh) + a.eps);
+    w[i] = wi;
+    store_weight(mw, i, wi);
 }
 
-__global__ void k_f32_to_bf16(const float* __restrict__ src, uint16_t* __restrict__ dst, long n) {
+__global__ void k_weights(const float* __restrict__ w, long n, MlpWeights mw) {
     const long i = static_cast<long>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i < n) dst[i] = to_bf16(src[i]);
-}
-
-// Normalised network output -> control sequence in the actuator box:
-// u = clamp(mid + half * y, u_min, u_max) per channel.
-// In residual mode (res_scale > 0) the output is added to the previous
-// sequence's scaled value carried in the features: ys = feat_U + res_scale y.
-__global__ void k_denorm(const float* __restrict__ y, const float* __restrict__ feat, int M, int T,
-                         int nu, FeatArgs F, float* __restrict__ U) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= M * T * nu) return;
-    const int ch = i % nu;
-    const int m = i / (T * nu), k = i % (T * nu);
-    const float ys = F.res_scale > 0.0f
-                         ? __builtin_fmaf(F.res_scale, y[i], feat[static_cast<size_t>(m) * F.in_dim + FEAT_BINS + 2 + k])
-                         : y[i];
-    const float mid = (F.umax[ch] + F.umin[ch]) * 0.5f;
-    const float half = (F.umax[ch] - F.umin[ch]) * 0.5f;
-    U[i] = fminf(fmaxf(mid + half * ys, F.umin[ch]), F.umax[ch]);
+    if (i < n) store_weight(mw, i, w[i]);
 }
 
 // Control sequences -> normalised training targets: y = (u - mid) / half.
@@ -322,52 +476,52 @@ hipError_t launch_features(const float* px, const float* py, const int* n_valid,
     return hipGetLastError();
 }
 
-hipError_t launch_to_bf16_padded(const float* src, int rows, int cols, int ld_src, uint16_t* dst,
-                                 int ld_dst, hipStream_t s) {
-    if (rows <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_to_bf16_padded, dim3((ld_dst + 255) / 256, rows), dim3(256), 0, s, src,
-                       rows, cols, ld_src, dst, ld_dst);
+hipError_t launch_mlp(MlpJobs& jobs, hipStream_t s) {
+    int blocks = 0;
+    for (int j = 0; j < jobs.n; ++j) {
+        MlpJob& g = jobs.job[j];
+        g.block0 = blocks;
+        if (g.kind == JOB_COLSUM) {
+            blocks += (g.N + 15) / 16;
+            continue;
+        }
+        if (g.kind == JOB_TRANSPOSE) {
+            g.tiles_n = (g.N + 31) / 32;
+            blocks += (g.M + 31) / 32 * g.tiles_n;
+            continue;
+        }
+        // 32 x 32 per wave (half the operand traffic) once that gives every
+        // SIMD of the chip a wave, 16 x 16 below (four times the waves).  The
+        // forward pass of 32768 rows (hidden 256) takes 148 us with the one and
+        // 224 with the other, of 4096 rows 38 and 42, of 2048 rows 43 and 32.
+        g.W = static_cast<long>((g.M + 31) / 32) * ((g.N + 31) / 32) >= 1024 ? 2 : 1;
+        // whole steps of 32 rows: the transposed copies are zero up to there
+        g.tiles_m = (g.M + 31) / 32 * 2 / g.W;
+        g.tiles_n = (g.N + 16 * g.W - 1) / (16 * g.W);
+        const long t = static_cast<long>(g.tiles_m) * g.tiles_n;
+        blocks += static_cast<int>((t + 3) / 4);
+    }
+    if (blocks == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_mlp, dim3(blocks), dim3(256), 0, s, jobs);
     return hipGetLastError();
 }
 
-hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
-    if (g.M <= 0 || g.N <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_gemm, dim3((g.N + GT - 1) / GT, (g.M + GT - 1) / GT), dim3(256), 0, s, g);
-    return hipGetLastError();
-}
-
-hipError_t launch_mse_grad(const float* out, const float* tgt, int M, int n_out, float* dout,
-                           uint16_t* dout_b, float* row_sq, float* loss, hipStream_t s) {
-    hipLaunchKernelGGL(k_mse_grad, dim3(M), dim3(256), 0, s, out, tgt, M, n_out, dout, dout_b, row_sq);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+hipError_t launch_loss(const float* out, const float* tgt, int M, int n_out, float* row_sq, float* loss,
+                       hipStream_t s) {
+    hipLaunchKernelGGL(k_row_sq, dim3(M), dim3(256), 0, s, out, tgt, n_out, row_sq);
     hipLaunchKernelGGL(k_loss_sum, dim3(1), dim3(LOSS_THREADS), 0, s, row_sq, M, n_out, loss);
     return hipGetLastError();
 }
 
-hipError_t launch_colsum(const float* d, int M, int N, float* out, hipStream_t s) {
-    hipLaunchKernelGGL(k_colsum, dim3((N + 63) / 64), dim3(64 * COLSUM_GROUPS), 0, s, d, M, N, out);
-    return hipGetLastError();
-}
-
 hipError_t launch_adam(float* w, const float* grad, float* m, float* v, long n, const AdamArgs& a,
-                       hipStream_t s) {
+                       const MlpWeights& mw, hipStream_t s) {
     hipLaunchKernelGGL(k_adam, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, s, w,
-                       grad, m, v, n, a);
+                       grad, m, v, n, a, mw);
     return hipGetLastError();
 }
 
-hipError_t launch_f32_to_bf16(const float* src, uint16_t* dst, long n, hipStream_t s) {
-    hipLaunchKernelGGL(k_f32_to_bf16, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, s,
-                       src, dst, n);
-    return hipGetLastError();
-}
-
-hipError_t launch_denorm(const float* y, const float* feat, int M, int T, int nu, const FeatArgs& F,
-                         float* U, hipStream_t s) {
-    const int n = M * T * nu;
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_denorm, dim3((n + 255) / 256), dim3(256), 0, s, y, feat, M, T, nu, F, U);
+hipError_t launch_weights(const float* w, long n, const MlpWeights& mw, hipStream_t s) {
+    hipLaunchKernelGGL(k_weights, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, s, w, n, mw);
     return hipGetLastError();
 }
 
