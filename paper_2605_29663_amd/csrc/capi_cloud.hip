@@ -34,14 +34,6 @@ int cloud_downsample(mppi_ctx ctx, const float* dxyz, int m, const float center[
     if (reach / cp->voxel >= static_cast<double>(1 << 29))
         return fail(ctx, MPPI_E_ARG, "cloud: voxel too small for the range (voxel index >= 2^29)");
     DeviceGuard g(ctx->device);
-    int cap = 256;
-    while (cap < 2 * m) cap <<= 1;
-    const size_t M = static_cast<size_t>(std::max(m, 1));
-    HIP_TRY(ctx, ctx->cloud_keys.ensure(sizeof(unsigned long long) * cap));
-    HIP_TRY(ctx, ctx->cloud_first.ensure(sizeof(int) * cap));
-    HIP_TRY(ctx, ctx->cloud_cell.ensure(sizeof(unsigned long long) * M));
-    HIP_TRY(ctx, ctx->cloud_r2.ensure(sizeof(uint32_t) * M));
-    HIP_TRY(ctx, ctx->cloud_misc.ensure(sizeof(int) * (2 * CLOUD_SCAN_BLOCK + 4 * 256 + 8 + 1)));
     CloudArgs a{};
     a.xyz = dxyz;
     a.m = m;
@@ -53,18 +45,44 @@ int cloud_downsample(mppi_ctx ctx, const float* dxyz, int m, const float center[
     a.voxel = cp->voxel;
     a.n_out = cp->n_out;
     CloudWork w{};
+    int cap = 256;
+    while (cap < 2 * m) cap <<= 1;
+    // The voxels of the range as a plain grid when they are no more than the
+    // hash table's slots or CLOUD_DENSE_MIN: 2^20 points take 56 us with a
+    // grid of 40000 cells and 83 with one of 10^6, hashed 85 and 102; 3000
+    // points with 160000 cells 39 and hashed 41, with 4 10^6 cells 54 and
+    // hashed 43.  The margins cover the rounding of the range test (relative 1e-6 of r_max) and of the
+    // quotient (2^-22 of its size); a squared range that overflows or loses
+    // its relative precision does not bound the coordinates.
+    const double vox = cp->voxel, margin = 2.0 + reach / vox * 0x1p-22;
+    const double r = static_cast<double>(cp->r_max) * (1.0 + 1e-6);
+    const double lx = std::floor((center[0] - r) / vox - margin), hx = std::floor((center[0] + r) / vox + margin);
+    const double ly = std::floor((center[1] - r) / vox - margin), hy = std::floor((center[1] + r) / vox + margin);
+    w.cells = cap;
+    if ((hx - lx + 1) * (hy - ly + 1) <= std::max(cap, CLOUD_DENSE_MIN) && std::isfinite(a.rmax2) &&
+        a.rmax2 >= 1e-30f) {
+        w.x0 = static_cast<int>(lx);
+        w.y0 = static_cast<int>(ly);
+        w.nx = static_cast<int>(hx - lx) + 1;
+        w.ny = static_cast<int>(hy - ly) + 1;
+        w.cells = w.nx * w.ny;
+    }
+    const size_t C = static_cast<size_t>(w.cells), words = (static_cast<size_t>(m) + 127) / 128 * 4;
+    if (w.nx == 0) HIP_TRY(ctx, ctx->cloud_keys.ensure(sizeof(unsigned long long) * C));
+    HIP_TRY(ctx, ctx->cloud_first.ensure(sizeof(int) * C));
+    HIP_TRY(ctx, ctx->cloud_cell.ensure(sizeof(uint2) * C));
+    HIP_TRY(ctx, ctx->cloud_r2.ensure(sizeof(uint32_t) * C));
+    HIP_TRY(ctx, ctx->cloud_misc.ensure(sizeof(int) * (words + CLOUD_BINS + 8)));
     w.keys = ctx->cloud_keys.as<unsigned long long>();
     w.first = ctx->cloud_first.as<int>();
-    w.cap_mask = cap - 1;
-    w.cell = ctx->cloud_cell.as<unsigned long long>();
-    w.r2 = ctx->cloud_r2.as<uint32_t>();
-    w.block_sums = ctx->cloud_misc.as<int2>();
-    w.hist = ctx->cloud_misc.as<int>() + 2 * CLOUD_SCAN_BLOCK;
-    w.state = w.hist + 4 * 256;
-    int* d_kept = w.state + 8;
-    HIP_TRY(ctx, launch_cloud(a, w, dx, dy, dvalid, d_kept, ctx->stream));
+    w.cand = ctx->cloud_cell.as<uint2>();
+    w.key = ctx->cloud_r2.as<uint32_t>();
+    w.kept = ctx->cloud_misc.as<uint32_t>();
+    w.hist = ctx->cloud_misc.as<int>() + words;
+    w.state = w.hist + CLOUD_BINS;
+    // the count goes straight to pinned memory
+    HIP_TRY(ctx, launch_cloud(a, w, dx, dy, dvalid, n_kept ? reinterpret_cast<int*>(ctx->h_out) : nullptr, ctx->stream));
     if (n_kept) {
-        HIP_TRY(ctx, hipMemcpyAsync(ctx->h_out, d_kept, sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
         HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
         std::memcpy(n_kept, ctx->h_out, sizeof(int));
     }

@@ -5,8 +5,9 @@
 
 namespace emppi {
 
-constexpr int CLOUD_SCAN_BLOCK = 1024;              // elements per scan block
-constexpr int CLOUD_MAX_POINTS = CLOUD_SCAN_BLOCK * CLOUD_SCAN_BLOCK;  // two-level scan
+constexpr int CLOUD_MAX_POINTS = 1 << 20;
+constexpr int CLOUD_BINS = 2048;         // ranges are binned by 16 octaves of 128
+constexpr int CLOUD_DENSE_MIN = 1 << 18;  // cells always held as a plain grid
 
 struct CloudArgs {
     const float* xyz;  // m x 3, row-major
@@ -18,15 +19,17 @@ struct CloudArgs {
 
 // Device workspace of one pre-processing call (sizes in elements).
 struct CloudWork {
-    unsigned long long* keys;  // cap: voxel hash table keys
-    int* first;                // cap: lowest point index per voxel
-    int cap_mask;              // cap - 1 (cap a power of two >= 2 m)
-    unsigned long long* cell;  // m: table slot of each kept point (~0 if dropped)
-    uint32_t* r2;              // m: squared range bits (KEY_NONE once known not a representative)
-    int2* block_sums;          // CLOUD_SCAN_BLOCK: (below, tie) sums per scan block
-    int* hist;                 // 4 x 256: one histogram per radix-select pass
-    int* state;                // 8: representatives, need, threshold, kept
+    int nx, ny, x0, y0;        // nx > 0: the cells are the voxels [x0, x0 + nx) x [y0, y0 + ny)
+    unsigned long long* keys;  // nx == 0: the cells are a hash table's slots, these its keys (a power of two >= 2 m)
+    int cells;
+    int* first;                // cells: lowest point index of the voxel
+    uint32_t* key;             // cells: squared range bits of that point, or CLOUD_NONE
+    uint32_t* kept;            // one bit per point, a multiple of 4 words
+    int* hist;                 // CLOUD_BINS: representatives per range bin
+    int* state;                // 8 (CLOUD_*)
+    uint2* cand;               // cells: (range bits, point) of the bin that the budget cuts
 };
+enum { CLOUD_KEPT = 0, CLOUD_BIN = 1, CLOUD_NEED = 2, CLOUD_CAND = 3 };
 
 hipError_t launch_cloud(const CloudArgs& a, const CloudWork& w, float* ox, float* oy,
                         unsigned char* valid, int* n_kept, hipStream_t s);
