@@ -329,7 +329,7 @@ int set_points(mppi_ctx ctx, const float* dx, const float* dy, const float* dvx,
     const PointSet out{ctx->px.as<float>(), ctx->py.as<float>(), ctx->pvx.as<float>(), ctx->pvy.as<float>(),
                        ctx->pidx.as<int>(), ctx->n_valid.as<int>(), ctx->pxy.as<float2>(),
                        ctx->pxy.as<float4>(), ctx->leaf.as<float4>(), ctx->leaf_vel.as<float4>(), ctx->super.as<float4>()};
-    HIP_TRY(ctx, launch_points(dx, dy, dvx, dvy, dvalid, n, out, ctx->points_ws.p, ctx->stream));
+    HIP_TRY(ctx, launch_points(dx, dy, dvx, dvy, dvalid, n, ctx->mid_tau, out, ctx->points_ws.p, ctx->stream));
     ctx->n_points = n;
     ctx->moving = moving;
     return MPPI_OK;

@@ -27,7 +27,7 @@
 // and one pass over memory for the points.  Measured against evaluating every
 // point (which ran at 86 - 92 % of the VALU issue rate): 81920 poses, 8192
 // corridor points, 16 vertices 1800 -> 165 us; 204800 poses, 20000 points of
-// which 30 % move, 4 boxes 2700 -> 850 us.
+// which 30 % move, 4 boxes 2700 -> 500 us.
 #pragma once
 #include "sdf_device.hpp"
 #include "wave_ops.hpp"
@@ -428,7 +428,7 @@ __device__ __forceinline__ void cull_block(const CullArgs& A, const float2* __re
                                 if (MOVING) {
                                     x = __builtin_fmaf(v.x, tc, x);
                                     y = __builtin_fmaf(v.y, tc, y);
-                                    r += v.z * ta + ts * (fabsf(v.x) + fabsf(v.y));
+                                    r += v.z * (fabsf(tc - v.w) + ts) + ts * (fabsf(v.x) + fabsf(v.y));
                                 }
                                 const float dx = x - gx, dy = y - gy;
                                 keep = !(__builtin_sqrtf(dx * dx + dy * dy) - r - lo_off > thr_l);
@@ -496,7 +496,7 @@ __device__ __forceinline__ void cull_block(const CullArgs& A, const float2* __re
                                         const float4 v = leaf_vel[i];
                                         x = __builtin_fmaf(v.x, tau, x);
                                         y = __builtin_fmaf(v.y, tau, y);
-                                        r = __builtin_fmaf(v.z, fabsf(tau), r);
+                                        r = __builtin_fmaf(v.z, fabsf(tau - v.w), r);
                                     }
                                     float lb, u;
                                     B(cells, x - q.x, y - q.y, lb, u);

@@ -40,9 +40,10 @@ struct StepArgs {
 // device so that a mask change needs no host round trip), with their
 // bounding hierarchy: leaf l covers points [8 l, 8 l + 8): (x, y) of one of
 // them, the largest distance from it to the others, unused; leaf_vel: that
-// point's velocity and the largest velocity difference to it; super node s
+// point's velocity, the largest velocity difference to it, and the time at
+// which the points were sorted and the leaf's distance holds; super node s
 // covers leaves [64 s, 64 s + 64): centre and radius of a circle around
-// them, and their largest speed.
+// them at time 0, and their largest speed.
 struct PointArgs {
     const float* x;
     const float* y;
@@ -76,7 +77,7 @@ struct PointWork {
 size_t points_work_bytes(int n);
 hipError_t points_setup();  // once per device, before the first launch_points
 hipError_t launch_points(const float* x, const float* y, const float* vx, const float* vy,
-                         const unsigned char* valid, int n, const PointSet& out, void* work, hipStream_t s);
+                         const unsigned char* valid, int n, float mid, const PointSet& out, void* work, hipStream_t s);
 
 // Bounds of a footprint's signed distance on a grid of cells in the body
 // frame, at the head of a device buffer that the cells follow.  A cell is one

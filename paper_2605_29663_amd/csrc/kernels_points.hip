@@ -64,6 +64,7 @@ struct PointIn {
     const float *x, *y, *vx, *vy;  // vx, vy may be nullptr
     const unsigned char* valid;    // may be nullptr
     int n;
+    float mid;                     // moving points are sorted and bounded by their positions at this time
 };
 
 __device__ __forceinline__ bool point_ok(const PointIn& in, int i) {
@@ -105,25 +106,44 @@ __device__ float2 sample_range(const PointIn& in, const float* a, int cells) {
 
 // Leaf over the points at(k) = (x, y, vx, vy), k < LEAF_POINTS (any repeated):
 // the point nearest to the centre of their bounding box represents the leaf;
-// radius = the largest distance to it, rv the largest velocity difference.
+// radius = the largest distance to it.  Moving points: the box and the radius
+// are those of time mid, in the nearest point's choice a velocity difference
+// counts as the way it makes in mid; vel = the representative's velocity, rv =
+// the largest velocity difference, mid, so that radius + rv |t - mid| bounds
+// the distances at time t.
 template <bool MOVING, typename At>
-__device__ __forceinline__ void make_leaf(At&& at, float4& leaf, float4& vel) {
+__device__ __forceinline__ void make_leaf(At&& at, float mid, float4& leaf, float4& vel) {
     float4 p[LEAF_POINTS];
     float x0 = INFINITY, x1 = -INFINITY, y0 = INFINITY, y1 = -INFINITY;
+    float u0 = INFINITY, u1 = -INFINITY, w0 = INFINITY, w1 = -INFINITY;
 #pragma unroll
     for (int k = 0; k < LEAF_POINTS; ++k) {
         p[k] = at(k);
-        x0 = fminf(x0, p[k].x);
-        x1 = fmaxf(x1, p[k].x);
-        y0 = fminf(y0, p[k].y);
-        y1 = fmaxf(y1, p[k].y);
+        const float x = MOVING ? p[k].x + p[k].z * mid : p[k].x, y = MOVING ? p[k].y + p[k].w * mid : p[k].y;
+        x0 = fminf(x0, x);
+        x1 = fmaxf(x1, x);
+        y0 = fminf(y0, y);
+        y1 = fmaxf(y1, y);
+        if (MOVING) {
+            u0 = fminf(u0, p[k].z);
+            u1 = fmaxf(u1, p[k].z);
+            w0 = fminf(w0, p[k].w);
+            w1 = fmaxf(w1, p[k].w);
+        }
     }
     const float cx = 0.5f * x0 + 0.5f * x1, cy = 0.5f * y0 + 0.5f * y1;
+    const float cu = 0.5f * u0 + 0.5f * u1, cw = 0.5f * w0 + 0.5f * w1;
     float best = INFINITY;
     float4 rep = p[0];
 #pragma unroll
     for (int k = 0; k < LEAF_POINTS; ++k) {
-        const float dx = p[k].x - cx, dy = p[k].y - cy, d = dx * dx + dy * dy;
+        float dx = p[k].x - cx, dy = p[k].y - cy, d = dx * dx + dy * dy;
+        if (MOVING) {
+            dx = p[k].x + p[k].z * mid - cx;
+            dy = p[k].y + p[k].w * mid - cy;
+            const float du = (p[k].z - cu) * mid, dw = (p[k].w - cw) * mid;
+            d = dx * dx + dy * dy + (du * du + dw * dw);
+        }
         if (d < best) {
             best = d;
             rep = p[k];
@@ -132,16 +152,25 @@ __device__ __forceinline__ void make_leaf(At&& at, float4& leaf, float4& vel) {
     float r2 = 0.0f, v2 = 0.0f;
 #pragma unroll
     for (int k = 0; k < LEAF_POINTS; ++k) {
-        const float dx = p[k].x - rep.x, dy = p[k].y - rep.y;
-        r2 = fmaxf(r2, dx * dx + dy * dy);
+        float dx = p[k].x - rep.x, dy = p[k].y - rep.y;
         if (MOVING) {
+            // from the differences: points of equal velocity stay finite
             const float ux = p[k].z - rep.z, uy = p[k].w - rep.w;
             v2 = fmaxf(v2, ux * ux + uy * uy);
+            dx += ux * mid;
+            dy += uy * mid;
         }
+        const float d = dx * dx + dy * dy;
+        r2 = fmaxf(r2, MOVING && !(d == d) ? INFINITY : d);
     }
-    // rounded up: the radius bounds the true distances
+    // rounded up: the radius bounds the true distances (moving: the sum of a
+    // difference and a way of opposite sign is exact to 2^-23 of the way)
+    const float rv = __builtin_sqrtf(v2) * 1.00001f;
     leaf = make_float4(rep.x, rep.y, __builtin_sqrtf(r2) * 1.00001f, 0.0f);
-    if (MOVING) vel = make_float4(rep.z, rep.w, __builtin_sqrtf(v2) * 1.00001f, 0.0f);
+    if (MOVING) {
+        leaf.z += 2e-6f * rv * mid;
+        vel = make_float4(rep.z, rep.w, rv, mid);
+    }
 }
 
 // Super node over a wave's 64 leaves (lane = leaf, on: the leaf exists):
@@ -152,7 +181,9 @@ __device__ __forceinline__ float4 make_super(bool on, float4 leaf, float4 vel) {
     const float y0 = wave_min(on ? leaf.y : INFINITY), y1 = -wave_min(on ? -leaf.y : INFINITY);
     const float cx = 0.5f * x0 + 0.5f * x1, cy = 0.5f * y0 + 0.5f * y1;
     const float dx = leaf.x - cx, dy = leaf.y - cy;
-    const float r = __builtin_sqrtf(dx * dx + dy * dy) * 1.00001f + leaf.z;
+    // moving: at time 0
+    float r = __builtin_sqrtf(dx * dx + dy * dy) * 1.00001f + (MOVING ? leaf.z + vel.z * vel.w * 1.00001f : leaf.z);
+    if (MOVING) r = r == r ? r : INFINITY;  // velocities that overflow
     float v = 0.0f;
     if (MOVING) v = __builtin_sqrtf(vel.x * vel.x + vel.y * vel.y) * 1.00001f + vel.z;
     return make_float4(cx, cy, -wave_min(on ? -r : INFINITY), MOVING ? -wave_min(on ? -v : INFINITY) : 0.0f);
@@ -268,6 +299,10 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_points_small(PointIn in, Poin
                 pvx[k % HV] = vx[b];
                 pvy[k % HV] = vy[b];
             }
+            if (MOVING && !PLACE) {  // the positions are only sorted by
+                px[k] += vx[b] * in.mid;
+                py[k] += vy[b] * in.mid;
+            }
         }
     }
     __syncthreads();
@@ -276,7 +311,8 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_points_small(PointIn in, Poin
     for (int k = 0; k < PT; ++k) {
         cr[k] = 0;
         if (okm >> k & 1) {
-            const unsigned c = cell_of(G, cell_bits, MOVING, mvm >> k & 1, px[k], py[k]);
+            const unsigned c = cell_of(G, cell_bits, MOVING, mvm >> k & 1, HV == PT ? px[k] + pvx[k % HV] * in.mid : px[k],
+                                       HV == PT ? py[k] + pvy[k % HV] * in.mid : py[k]);
             const unsigned sh = (c & 1) * 16;
             cr[k] = (c << 16) | ((atomicAdd(&hist[c >> 1], 1u << sh) >> sh) & 0xFFFFu);
         }
@@ -398,7 +434,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_points_small(PointIn in, Poin
                 const bool on = k < m;
                 return make_float4(on ? x[k] : x[0], on ? y[k] : y[0], MOVING ? (on ? vx[k] : vx[0]) : 0.0f,
                                    MOVING ? (on ? vy[k] : vy[0]) : 0.0f);
-            }, leaf, vel);
+            }, in.mid, leaf, vel);
             const int gl = w0 / LEAF_POINTS + l;
             out.leaf[gl] = leaf;
             if (MOVING) out.leaf_vel[gl] = vel;
@@ -437,7 +473,8 @@ __global__ __launch_bounds__(256) void k_points_count(PointIn in, PointWork w, b
     uint2 cr = make_uint2(~0u, ~0u);
     if (point_ok(in, i)) {
         const Grid G{w.grid[0], w.grid[1], w.grid[2], w.grid[3]};
-        cr.x = cell_of(G, LARGE_CELL_BITS, moving, moving && point_moves(in, i), in.x[i], in.y[i]);
+        cr.x = cell_of(G, LARGE_CELL_BITS, moving, moving && point_moves(in, i),
+                       in.x[i] + (in.vx ? in.vx[i] * in.mid : 0.0f), in.y[i] + (in.vy ? in.vy[i] * in.mid : 0.0f));
         cr.y = atomicAdd(&w.cells[cr.x], 1u);
     }
     w.cell_rank[i] = cr;
@@ -510,7 +547,7 @@ __global__ __launch_bounds__(256) void k_points_place(PointIn in, PointSet out,
 
 // One wave per super node: lane = leaf.
 template <bool MOVING>
-__global__ __launch_bounds__(WAVE) void k_points_nodes(PointSet out) {
+__global__ __launch_bounds__(WAVE) void k_points_nodes(PointSet out, float mid) {
     const int nv = *out.n_valid;
     const int nleaf = (nv + LEAF_POINTS - 1) / LEAF_POINTS;
     if (static_cast<int>(blockIdx.x) * SUPER_LEAVES >= nleaf) return;
@@ -524,7 +561,7 @@ __global__ __launch_bounds__(WAVE) void k_points_nodes(PointSet out) {
             if (MOVING) return out.xyv[j];
             const float2 o = out.xy[j];
             return make_float4(o.x, o.y, 0.0f, 0.0f);
-        }, leaf, vel);
+        }, mid, leaf, vel);
         out.leaf[l] = leaf;
         if (MOVING) out.leaf_vel[l] = vel;
     }
@@ -551,9 +588,9 @@ size_t small_lds(int n, int cell_bits, bool moving) {
 }
 
 template <bool MOVING>
-hipError_t launch_nodes(const PointSet& out, int n, hipStream_t s) {
+hipError_t launch_nodes(const PointSet& out, int n, float mid, hipStream_t s) {
     const int nsuper = (n + LEAF_POINTS * SUPER_LEAVES - 1) / (LEAF_POINTS * SUPER_LEAVES);
-    hipLaunchKernelGGL((k_points_nodes<MOVING>), dim3(nsuper), dim3(WAVE), 0, s, out);
+    hipLaunchKernelGGL((k_points_nodes<MOVING>), dim3(nsuper), dim3(WAVE), 0, s, out, mid);
     return hipGetLastError();
 }
 
@@ -565,7 +602,7 @@ hipError_t launch_small(const PointIn& in, const PointSet& out, unsigned* positi
                        positions);
     if (PT > 8) {
         hipLaunchKernelGGL(k_points_place, dim3((in.n + 255) / 256), dim3(256), 0, s, in, out, positions, MOVING);
-        return launch_nodes<MOVING>(out, in.n, s);
+        return launch_nodes<MOVING>(out, in.n, in.mid, s);
     }
     return hipGetLastError();
 }
@@ -605,8 +642,8 @@ size_t points_work_bytes(int n) {
 }
 
 hipError_t launch_points(const float* x, const float* y, const float* vx, const float* vy,
-                         const unsigned char* valid, int n, const PointSet& out, void* work, hipStream_t s) {
-    const PointIn in{x, y, vx, vy, valid, n};
+                         const unsigned char* valid, int n, float mid, const PointSet& out, void* work, hipStream_t s) {
+    const PointIn in{x, y, vx, vy, valid, n, mid};
     const bool moving = vx || vy;
     if (n <= POINTS_DIRECT_MAX) {
         hipLaunchKernelGGL(k_points_direct, dim3(1), dim3(POINTS_DIRECT_MAX), 0, s, in, out, moving);
@@ -632,7 +669,7 @@ hipError_t launch_points(const float* x, const float* y, const float* vx, const 
     hipLaunchKernelGGL(k_points_scan_top, dim3(1), dim3(256), 0, s, w, out.n_valid);
     hipLaunchKernelGGL(k_points_positions, g, b, 0, s, n, w);
     hipLaunchKernelGGL(k_points_place, g, b, 0, s, in, out, w.positions, moving);
-    return moving ? launch_nodes<true>(out, n, s) : launch_nodes<false>(out, n, s);
+    return moving ? launch_nodes<true>(out, n, mid, s) : launch_nodes<false>(out, n, mid, s);
 }
 
 }  // namespace emppi
