@@ -99,9 +99,9 @@ FootTable foot_head(int kind, const float* host, int count) {
     // values lie within [-half size, diagonal of the grid]
     F.base = static_cast<float>(-0.6 * std::hypot(W, H) - 2.0 * std::hypot(dx, dy));
     F.quantum = static_cast<float>((1.6 * std::hypot(w0, h0) + 3.0 * std::hypot(dx, dy)) / 65000.0);
-    F.err_cell = static_cast<float>(0.51 * std::hypot(dx, dy) + F.quantum + 1e-5 * reach);
+    F.err_cell = static_cast<float>(0.51 * std::hypot(dx, dy) + 8 * F.quantum + 1e-5 * reach);
     // the gradient's components are rounded to 1 / 127
-    F.err_linear = static_cast<float>((dx + dy) * 0.26 / 127.0 + F.quantum + 1e-5 * reach);
+    F.err_linear = static_cast<float>((dx + dy) * 0.26 / 127.0 + 8 * F.quantum + 1e-5 * reach);
     return F;
 }
 

@@ -26,7 +26,7 @@
 // many waves with few poses each, LDS for everything that is read at random
 // and one pass over memory for the points.  Measured against evaluating every
 // point (which ran at 86 - 92 % of the VALU issue rate): 81920 poses, 8192
-// corridor points, 16 vertices 1800 -> 165 us; 204800 poses, 20000 points of
+// corridor points, 16 vertices 1800 -> 135 us; 204800 poses, 20000 points of
 // which 30 % move, 4 boxes 2700 -> 500 us.
 #pragma once
 #include "sdf_device.hpp"
@@ -118,7 +118,7 @@ __device__ __forceinline__ float threshold(float ub, float slack) {
 // relative to the pose position.
 struct PoseBounds {
     float ax, bx, ay, by, ox, oy;  // cell coordinates: fma(dx, ax, fma(dy, bx, ox)), ...
-    float dx, dy, gdx, gdy, base, quantum, err_cell, err_linear, mx, my;
+    float dx, dy, gdx, gdy, base, quantum, err_step, err_linear, mx, my;
     unsigned nx;
 
     __device__ __forceinline__ void init(const FootTable& F, float c, float s) {
@@ -134,7 +134,7 @@ struct PoseBounds {
         gdy = F.dy * (1.0f / 127.0f);
         base = F.base;
         quantum = F.quantum;
-        err_cell = F.err_cell;
+        err_step = (F.err_cell - F.err_linear) * (1.0f / 7.0f);
         err_linear = F.err_linear;
         nx = F.nx;
         mx = static_cast<float>(F.nx) - 0.01f;
@@ -153,7 +153,7 @@ struct PoseBounds {
         float est = __builtin_fmaf(static_cast<float>(w & 0xFFFFu), quantum, base);
         est = __builtin_fmaf(static_cast<float>(static_cast<int>(w << 8) >> 24), tx, est);
         est = __builtin_fmaf(static_cast<float>(static_cast<int>(w) >> 24), ty, est);
-        const float err = w > 0xFFFFu ? err_linear : err_cell;
+        const float err = __builtin_fmaf(static_cast<float>(w & 7u), err_step, err_linear);
         const float l = est - err;
         lb = l;
         ub = est + err;

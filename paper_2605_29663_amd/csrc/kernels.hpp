@@ -81,13 +81,14 @@ hipError_t launch_points(const float* x, const float* y, const float* vx, const 
 
 // Bounds of a footprint's signed distance on a grid of cells in the body
 // frame, at the head of a device buffer that the cells follow.  A cell is one
-// word, (v, gx, gy) in bits 0-15, 16-23 and 24-31 (gx, gy signed): the
-// distance at its centre lies in [base + quantum v, base + quantum (v + 1)].
-// Where one straight feature is nearest to the whole cell the distance is
-// linear in it, with the gradient (gx, gy) / 127, and est = base + quantum v
-// + gradient . offset from the centre is exact to err_linear; elsewhere gx =
-// gy = 0 and est is exact to err_cell, half the cell's diagonal (the distance
-// changes by at most the way travelled).  The grid covers the footprint's
+// word, (v, gx, gy) in bits 0-15, 16-23 and 24-31 (gx, gy signed): est = base
+// + quantum v + (gx, gy) / 127 . offset from the centre is the distance up to
+// err_linear + c (err_cell - err_linear) / 7, where c is v's lowest 3 bits (the
+// others are the distance at the centre, 8 quantum the step).  c = 0 where the
+// distance is linear in the cell; 1 .. 6 where it bends slowly (beside a
+// corner, the more the nearer); 7 with no gradient elsewhere: err_cell is half
+// the cell's diagonal, and the distance changes by at most the way travelled.
+// The grid covers the footprint's
 // bounding box and a margin around it, in which every border cell's lower
 // bound is positive; a point outside projects onto the grid's rectangle,
 // which is convex, so with the distance a to the projection and the
