@@ -296,14 +296,16 @@ MPPI_API int mppi_step(mppi_ctx ctx, const mppi_params* prm, const float* q0, fl
 
 /* Tile-shape autotuner for the fused transform + signed distance + min
  * stage of mppi_step: for prm's shape and the footprint and points currently
- * set, time every candidate (workgroup size in {64, 128, 256} poses, number of
- * point chunks) on one sampled step with HIP events (reps launches each) and
- * keep the fastest for this context; mppi_step then uses it whenever the
+ * set, time every candidate (the default rule, and workgroup sizes in {64,
+ * 128, 256} poses with numbers of point chunks; the bounded search of larger
+ * sets reads the first as poses per workgroup and splits only sets above 32768
+ * points) on one sampled step with HIP events (reps launches each) and keep the
+ * fastest for this context; mppi_step then uses it whenever the
  * shape (kind, padded primitive count, moving points, K*T, N) matches.  With
  * prm->validate the point-chunk count of the validation pass (T poses) is
  * tuned the same way.  out_block / out_nchunk (host, may be NULL) receive
- * the sampled pass's choice.  Results do not depend on the choice
- * (bit-identical).  Synchronous.                                            */
+ * the sampled pass's choice (0, 0: the default rule).  Results do not depend on
+ * the choice (bit-identical).  Synchronous.                                            */
 MPPI_API int mppi_autotune(mppi_ctx ctx, const mppi_params* prm, int reps, int* out_block,
                            int* out_nchunk);
 
@@ -373,7 +375,8 @@ MPPI_API int mppi_batch_refresh(mppi_batch b);
 MPPI_API int mppi_step_batched(mppi_batch b, const float* q0, float* dU, const uint64_t* seeds,
                                const uint64_t* steps, float* u_out, int* valid_out, int use_graph);
 
-/* Tile autotuner of the batch: after a warm-up, times the persistent
+/* Tile autotuner of the batch (for its scenes of few points; the bounded search
+ * of the others has a fixed plan): after a warm-up, times the persistent
  * signed-distance pass for queue items of 2^16 .. 2^26 point-primitive pairs
  * (reps launches each, HIP events, a forward and a backward sweep, the
  * faster of the two kept) and re-plans with the fastest.
