@@ -110,7 +110,9 @@ __device__ __forceinline__ float signed_sqrt_fast(float s) {
 __device__ __forceinline__ float threshold(float ub, float slack) {
     // every bound and distance is computed with relative errors of a few
     // 2^-24 of the distance or of the footprint's size; 1e-4 covers them
-    // with a wide margin (and rotations up to 1e-5 off unit length)
+    // with a wide margin (and rotations up to 1e-5 off unit length).  Errors of
+    // the coordinates' size (a group's centre, a moving point's position) are in
+    // the group's spread and in the caller's slack.
     return ub + 1e-4f * fabsf(ub) + slack;
 }
 
@@ -334,8 +336,9 @@ __device__ __forceinline__ void cull_block(const CullArgs& A, const float2* __re
         if (lane == 0) {
             S.group[0] = gx;
             S.group[1] = gy;
-            // rounding of the moving points' positions grows with the coordinates
-            S.group[2] = spread * 1.0001f + (MOVING ? 2e-6f * (fabsf(gx) + fabsf(gy) + spread) : 0.0f);
+            // rounding of the centres (and of the moving points' positions) grows
+            // with the coordinates
+            S.group[2] = spread * 1.0001f + 2e-6f * (fabsf(gx) + fabsf(gy) + spread);
             S.group[3] = tc;
             S.group[4] = ts * 1.0001f;
             S.group[5] = ta * 1.0001f;
