@@ -116,6 +116,9 @@ __device__ __forceinline__ float threshold(float ub, float slack) {
     return ub + 1e-4f * fabsf(ub) + slack;
 }
 
+// c^2 + s^2 of a rotation, up to this
+constexpr float ROTATION_TOL = 1e-5f;
+
 // Bounds of the signed distance from the footprint table for points given
 // relative to the pose position.
 struct PoseBounds {
@@ -141,6 +144,41 @@ struct PoseBounds {
         nx = F.nx;
         mx = static_cast<float>(F.nx) - 0.01f;
         my = static_cast<float>(F.ny) - 0.01f;
+    }
+
+    // For (c, s) of length k that is no rotation (the caller's poses may be
+    // anything, a rotation rounded to 16 bits for one).  The evaluators then see
+    // the footprint scaled by k (SCALED: a polygon, whose vertices are turned by
+    // (c, s)) or the points scaled by k (a cover): the table at (c, s) / k^2,
+    // its distances times k, or the table at (c, s).  Returns k, and the factor
+    // of distances between points in `apart`; without bounds (NaN) where k is no
+    // size to calculate with.
+    template <bool SCALED>
+    __device__ __forceinline__ float init_scaled(const FootTable& F, float c, float s, float& apart) {
+        const float k2 = __builtin_fmaf(c, c, s * s);
+        apart = 1.0f;
+        if (fabsf(k2 - 1.0f) <= ROTATION_TOL) {
+            init(F, c, s);
+            return 1.0f;
+        }
+        const bool usable = k2 > 1e-6f && k2 < 1e6f;
+        const float k = usable ? __builtin_amdgcn_sqrtf(k2) : 1.0f;
+        if (SCALED) {
+            init(F, c / k2, s / k2);
+            dx *= k;
+            dy *= k;
+            gdx *= k;
+            gdy *= k;
+            base *= k;
+            quantum *= k;
+            err_step *= k;
+            err_linear *= k;
+        } else {
+            init(F, c, s);
+            apart = k;
+        }
+        if (!usable) base = NAN;
+        return fmaxf(k, 1.0f);
     }
 
     __device__ __forceinline__ void operator()(const uint32_t* cells, float px, float py, float& lb,
@@ -182,6 +220,7 @@ constexpr int DPP_ROR1 = 0x121, DPP_ROR2 = 0x122, DPP_ROR4 = 0x124, DPP_ROR8 = 0
 template <int HB>
 struct EvalPoly {
     static constexpr int WAVES = HB <= 2 ? 6 : 4;  // per SIMD, without scratch in the loops
+    static constexpr bool SCALED = true;           // PoseBounds::init_scaled
     PolyPart<HB, EVAL_LANES> F;
     __device__ __forceinline__ void init(const float2* verts, const float4*, int n, int part, float4 q) {
         F.init(verts, part * HB, q.z, q.w);
@@ -213,6 +252,7 @@ struct EvalPoly {
 template <int NB>
 struct EvalRect {
     static constexpr int WAVES = 6;
+    static constexpr bool SCALED = false;
     float4 bx[NB];
     float c, s;
     __device__ __forceinline__ void init(const float2*, const float4* rects, int n, int part, float4 q) {
@@ -238,7 +278,7 @@ struct EvalRect {
     }
 };
 
-enum { CULL_ANY = 1, CULL_ALL_POINTS = 2 };  // a finite pose exists; a pose needs every point
+enum { CULL_ANY = 1, CULL_SCALED = 2 };  // a finite pose exists; one whose (cos, sin) is no rotation
 
 // `tiles` tiles of nw P poses of A from g0, gstep apart (P per wave, wave w the
 // w-th P of a tile), against the leaves of the super nodes [s0, s1): each pose's minimum
@@ -279,7 +319,7 @@ __device__ __forceinline__ void cull_block(const CullArgs& A, const float2* __re
     if (wid == 0) {
         float xmin = INFINITY, xmax = INFINITY, ymin = INFINITY, ymax = INFINITY;  // maxima negated
         float tmin = INFINITY, tmax = INFINITY;
-        bool any = false, all = false;
+        bool any = false, scaled = false;
         float ccx[CULL_WAVES * CULL_POSES / WAVE], ccy[CULL_WAVES * CULL_POSES / WAVE];
         bool ok[CULL_WAVES * CULL_POSES / WAVE];
 #pragma unroll
@@ -300,9 +340,8 @@ __device__ __forceinline__ void cull_block(const CullArgs& A, const float2* __re
                 O.besti[o] = -1;
                 if (ok[k]) {
                     any = true;
-                    // not a rotation (the caller's poses may be anything): the
-                    // bounds do not hold, every point is evaluated
-                    if (!(fabsf(__builtin_fmaf(q.z, q.z, q.w * q.w) - 1.0f) <= 1e-5f)) all = true;
+                    // no rotation: the group's circles do not hold
+                    if (!(fabsf(__builtin_fmaf(q.z, q.z, q.w * q.w) - 1.0f) <= ROTATION_TOL)) scaled = true;
                     ccx[k] = q.x + (q.z * F.cx - q.w * F.cy);
                     ccy[k] = q.y + (q.w * F.cx + q.z * F.cy);
                     xmin = fminf(xmin, ccx[k]);
@@ -332,7 +371,7 @@ __device__ __forceinline__ void cull_block(const CullArgs& A, const float2* __re
             ts = 0.5f * (tmax - tmin);
             ta = fmaxf(fabsf(tmin), fabsf(tmax));
         }
-        const int fl = (__ballot(any) ? CULL_ANY : 0) | (__ballot(all) ? CULL_ALL_POINTS : 0);
+        const int fl = (__ballot(any) ? CULL_ANY : 0) | (__ballot(scaled) ? CULL_SCALED : 0);
         if (lane == 0) {
             S.group[0] = gx;
             S.group[1] = gy;
@@ -353,13 +392,13 @@ __device__ __forceinline__ void cull_block(const CullArgs& A, const float2* __re
     if (flags & CULL_ANY) {
         const float gx = S.group[0], gy = S.group[1], spread = S.group[2];
         const float tc = S.group[3], ts = S.group[4], ta = S.group[5];
-        const bool all = flags & CULL_ALL_POINTS;
+        const bool scaled = flags & CULL_SCALED;
         // distance bounds of a circle (x, y, r) to any pose of the group:
         // >= D - r - spread - radius and <= D + r + spread + centre_d
         const float lo_off = spread + F.radius, hi_off = spread + F.centre_d;
         // up to 64 leaves: list them as they are
         const bool few = s1 - s0 <= 1 || direct;
-        if (!few && !all) {
+        if (!few && !scaled) {
             float m = INFINITY;
             for (int s = s0 + t; s < s1; s += nthreads) {
                 const float4 c = A.pts.super[s];
@@ -373,11 +412,11 @@ __device__ __forceinline__ void cull_block(const CullArgs& A, const float2* __re
         // CULL_LEAVES at a time
         for (int sb = s0; sb < s1; sb += CULL_SUPERS) {
             if (!direct) __syncthreads();
-            const float thr_s = all ? INFINITY : threshold(dkey_value(S.ub_super), slack);
+            const float thr_s = scaled ? INFINITY : threshold(dkey_value(S.ub_super), slack);
             const int se = min(sb + CULL_SUPERS, s1);
             for (int s = sb + t; s < se && !direct; s += nthreads) {
                 bool keep = true;
-                if (!few && !all) {
+                if (!few && !scaled) {
                     const float4 c = A.pts.super[s];
                     const float dx = c.x - gx, dy = c.y - gy;
                     keep = !(__builtin_sqrtf(dx * dx + dy * dy) - (c.z + c.w * ta) - lo_off > thr_s);
@@ -387,7 +426,7 @@ __device__ __forceinline__ void cull_block(const CullArgs& A, const float2* __re
             if (!direct) __syncthreads();
             const int ns = direct ? 1 : __builtin_amdgcn_readfirstlane(S.n_super);
             // the leaf nearest to the group bounds every pose's minimum
-            if (!few && !all) {
+            if (!few && !scaled) {
                 float m = INFINITY;
                 for (int k = wid; k < ns; k += nw) {
                     const int l = (sb + S.supers[k]) * SUPER_LEAVES + lane;
@@ -408,7 +447,7 @@ __device__ __forceinline__ void cull_block(const CullArgs& A, const float2* __re
                 if (lane == 0) atomicMin(&S.ub_leaf, dkey(m));
                 __syncthreads();
             }
-            const float thr_l = all ? INFINITY : threshold(dkey_value(S.ub_leaf), slack);
+            const float thr_l = scaled ? INFINITY : threshold(dkey_value(S.ub_leaf), slack);
             for (int k0 = 0; k0 < ns;) {
                 // list leaves while the next super node's certainly fit
                 int k1 = k0, nlist = 0;
@@ -426,7 +465,7 @@ __device__ __forceinline__ void cull_block(const CullArgs& A, const float2* __re
                         if (keep) {
                             c = A.pts.leaf[l];
                             if (MOVING) v = A.pts.leaf_vel[l];
-                            if (!few && !all) {
+                            if (!few && !scaled) {
                                 float x = c.x, y = c.y, r = c.z;
                                 if (MOVING) {
                                     x = __builtin_fmaf(v.x, tc, x);
@@ -455,7 +494,7 @@ __device__ __forceinline__ void cull_block(const CullArgs& A, const float2* __re
                 // ---- each wave: its poses against the listed leaves
                 int p = 0, pf = 0;         // pose in progress, first pose with queued points
                 int nq = 0, nq0 = 0, nkeep = 0, c0 = 0;  // queued in all, before this pose
-                float ub = INFINITY, pslack = slack, tau = 0.0f;
+                float ub = INFINITY, pslack = slack, tau = 0.0f, apart = 1.0f;
                 float4 q = make_float4(0.f, 0.f, 1.f, 0.f);
                 PoseBounds B;
                 bool fresh = true;
@@ -464,8 +503,11 @@ __device__ __forceinline__ void cull_block(const CullArgs& A, const float2* __re
                         if (fresh) {
                             q = wave_uniform(Wv.pose[p]);
                             tau = MOVING ? wave_uniform(Wv.tau[p]) : 0.0f;
-                            B.init(F, q.z, q.w);
                             pslack = slack + (MOVING ? 2e-6f * (fabsf(q.x) + fabsf(q.y)) : 0.0f);
+                            if (scaled)
+                                pslack *= B.init_scaled<Eval::SCALED>(F, q.z, q.w, apart);
+                            else
+                                B.init(F, q.z, q.w);
                             nkeep = 0;
                             c0 = 0;
                             nq0 = nq;
@@ -503,7 +545,7 @@ __device__ __forceinline__ void cull_block(const CullArgs& A, const float2* __re
                                     }
                                     float lb, u;
                                     B(cells, x - q.x, y - q.y, lb, u);
-                                    lbs[b] = lb - r;
+                                    lbs[b] = __builtin_fmaf(-r, apart, lb);
                                     m = fminf(m, u);
                                     // one batch at a time: interleaved, the
                                     // batches' registers would spill
@@ -511,7 +553,7 @@ __device__ __forceinline__ void cull_block(const CullArgs& A, const float2* __re
                                 }
                             }
                             ub = fminf(wave_min(m), signed_sqrt_fast(Wv.best[p]));
-                            const float thr = all ? INFINITY : threshold(ub, pslack);
+                            const float thr = threshold(ub, pslack);
 #pragma unroll
                             for (int b = 0; b < CULL_LEAVES / WAVE; ++b)
                                 if (b * WAVE < nlist) {
@@ -570,7 +612,7 @@ __device__ __forceinline__ void cull_block(const CullArgs& A, const float2* __re
                                 }
                             }
                             ub = fminf(ub, wave_min(m));
-                            const float thr = all ? INFINITY : threshold(ub, pslack);
+                            const float thr = threshold(ub, pslack);
 #pragma unroll
                             for (int k = 0; k < CULL_CHUNK; ++k)
                                 if (c0 + k * WAVE < nkeep * LEAF_POINTS) {
@@ -589,7 +631,7 @@ __device__ __forceinline__ void cull_block(const CullArgs& A, const float2* __re
                             // most were queued before the pose's bound was
                             // final: filter them once more
                             wave_lds_fence();
-                            const float thr = all ? INFINITY : threshold(ub, pslack);
+                            const float thr = threshold(ub, pslack);
                             const int n = nq;
                             nq = nq0;
                             for (int b = nq0; b < n; b += WAVE) {
