@@ -72,7 +72,7 @@ struct PointWork {
     uint2* cell_rank;     // this and the rest above POINTS_SMALL_MAX
     unsigned* cells;
     int* block_sums;
-    float* grid;  // lo x, lo y, cells per metre x, y
+    float* grid;  // sampled range: lo and length in x, in y
 };
 size_t points_work_bytes(int n);
 hipError_t points_setup();  // once per device, before the first launch_points
