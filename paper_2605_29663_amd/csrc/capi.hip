@@ -110,10 +110,11 @@ FootTable foot_head(int kind, const float* host, int count) {
 int upload_foot(mppi_ctx ctx, DevBuf& buf, int kind, const float* host, int count) {
     const FootTable F = foot_head(kind, host, count);
     HIP_TRY(ctx, buf.ensure(foot_table_bytes()));
-    HIP_TRY(ctx, hipMemcpy(buf.p, &F, sizeof F, hipMemcpyHostToDevice));
+    HIP_TRY(ctx, hipMemcpy(buf.p, &F, offsetof(FootTable, far), hipMemcpyHostToDevice));
     HIP_TRY(ctx, launch_foot_table(kind, buf.as<FootTable>(),
                                    kind == 0 ? ctx->poly_tab_a.as<float4>() : ctx->rects.as<float4>(),
-                                   kind == 0 ? ctx->poly_tab_b.as<float4>() : nullptr, count, ctx->stream));
+                                   kind == 0 ? ctx->poly_tab_b.as<float4>() : nullptr,
+                                   kind == 0 ? ctx->poly_verts.as<float2>() : nullptr, count, ctx->stream));
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
     return MPPI_OK;
 }

@@ -17,17 +17,24 @@
 //      table of the footprint's signed distance in the body frame, about 25
 //      instructions per 64 of them whatever the number of edges; the points
 //      whose lower bound does not exceed the pose's upper bound (a handful)
-//      are queued;
+//      are queued.  The table's bounds are loose far from the footprint; a pose
+//      that keeps many leaves or points goes through them once more with the
+//      corner that reaches furthest in the point's direction (FootTable::far);
 //   3. when the queue fills, and at the end, the wave evaluates the queued
 //      points exactly, 16 lanes per pose with the edges split among them
 //      (the same operations on the same operands, hence the same bits, as an
-//      evaluation of every point by one lane).
+//      evaluation of every point by one lane); many points of one pose go one
+//      per lane where the footprint is boxes.
 // It is bound by the latency of the short dependent phases of step 2, hence
 // many waves with few poses each, LDS for everything that is read at random
 // and one pass over memory for the points.  Measured against evaluating every
 // point (which ran at 86 - 92 % of the VALU issue rate): 81920 poses, 8192
 // corridor points, 16 vertices 1800 -> 135 us; 204800 poses, 20000 points of
-// which 30 % move, 4 boxes 2700 -> 500 us.
+// which 30 % move, 4 boxes 2700 -> 500 us.  Sets that the bounds cannot thin out
+// cost more than every point would: 20480 poses against 8192 points, with 16
+// edges / 4 boxes, a field 60 / 57 us, a wall 20 m away 350 / 325, a ring of 5 m
+// 640 / 340, all in one place 2740 / 815, every point evaluated 510 - 620 / 122
+// (before FootTable::far: wall 2300 / 1760, ring 2430 / 2010).
 #pragma once
 #include "sdf_device.hpp"
 #include "wave_ops.hpp"
@@ -40,13 +47,20 @@ constexpr int CULL_LEAVES = 320;       // leaves listed at a time (LDS)
 constexpr int CULL_QUEUE = 256;        // queued points per wave (LDS)
 constexpr int CULL_CHUNK = 2;          // 64-point batches bounded before they are filtered
 constexpr int CULL_REFILTER = 8;       // a pose's queued points worth a second filter
+// Queued points and kept leaves of a pose that call for the closer bounds: a
+// field's or corridor's poses keep about 3 and 30 and pay only the comparison;
+// 48 leaves instead of 128 took the corridor from 230 to 276 us a step.
+constexpr int CULL_FAR = 48;
+constexpr int CULL_FAR_LEAVES = 128;
+constexpr int CULL_EACH = 24;          // a pose's queued points that are evaluated one per lane (boxes)
 constexpr int CULL_SUPERS = 512;       // super nodes examined at a time
 
 // LDS of a workgroup.
 struct CullShared {
     float4 leaf[CULL_LEAVES];                 // x, y, radius, leaf index (no hierarchy: the static points)
+    float4 far[FAR_BINS];                     // FootTable::far
     unsigned short supers[CULL_SUPERS];
-    float group[8];                           // centre x, y, spread, tau centre, spread, max |tau|
+    float group[8];                           // centre x, y, spread, tau centre, spread, max |tau|, table's centre x, y
     unsigned ub_super, ub_leaf;               // ordered keys of the workgroup's upper bounds
     int n_super, n_leaf, flags;
 };
@@ -54,18 +68,17 @@ struct CullWave {
     float4 pose[CULL_POSES];
     float tau[CULL_POSES];
     float best[CULL_POSES];                   // signed squared distance so far
-    int besti[CULL_POSES];                    // caller's index attaining it (argmin)
     float2 queue[CULL_QUEUE];                 // points (at the pose's time), pose after pose
     unsigned short leaf[CULL_LEAVES];         // list positions of the leaves a pose keeps
-    int begin[CULL_POSES], end[CULL_POSES];   // each pose's part of the queue
+    unsigned short begin[CULL_POSES], end[CULL_POSES];  // each pose's part of the queue
 };
 
 // Order of the dynamic LDS: footprint table, CullShared, one CullWave per
 // wave, then (moving points) the listed leaves' velocities, then (argmin) the
-// queued points' caller's indices.
+// queued points' caller's indices and those attaining the poses' minima.
 __host__ __device__ inline size_t cull_lds_bytes(int nw, bool moving, bool argmin) {
     return sizeof(uint32_t) * FOOT_CELLS + sizeof(CullShared) + sizeof(CullWave) * nw +
-           (moving ? sizeof(float4) * CULL_LEAVES : 0) + (argmin ? sizeof(int) * CULL_QUEUE * nw : 0);
+           (moving ? sizeof(float4) * CULL_LEAVES : 0) + (argmin ? sizeof(int) * (CULL_QUEUE + CULL_POSES) * nw : 0);
 }
 
 // One launch's view of a pass: poses, points, footprint.
@@ -175,10 +188,10 @@ struct PoseBounds {
             err_linear *= k;
         } else {
             init(F, c, s);
-            apart = k;
+            apart = wave_uniform(k);
         }
         if (!usable) base = NAN;
-        return fmaxf(k, 1.0f);
+        return wave_uniform(fmaxf(k, 1.0f));
     }
 
     __device__ __forceinline__ void operator()(const uint32_t* cells, float px, float py, float& lb,
@@ -206,6 +219,27 @@ struct PoseBounds {
     }
 };
 
+// Interval of FootTable::far that holds the direction of (x, y): the
+// pseudo-angle y / (|x| + |y|), continued over the left half plane, from -1 to 3.
+__device__ __forceinline__ int far_bin(float x, float y) {
+    const float t = y * __builtin_amdgcn_rcpf(fabsf(x) + fabsf(y));
+    const float a = x >= 0.0f ? t : 2.0f - t;
+    return static_cast<int>(__builtin_fmaf(a, FAR_BINS / 4.0f, FAR_BINS / 4.0f)) & (FAR_BINS - 1);  // (NaN: 0)
+}
+
+// Bounds of the signed distance from FootTable::far for a point relative to
+// the pose q (a rotation).
+__device__ __forceinline__ void far_bounds(const CullShared& S, float4 q, float px, float py, float& lb, float& ub) {
+    const float x = __builtin_fmaf(q.z, px, __builtin_fmaf(q.w, py, -S.group[6]));
+    const float y = __builtin_fmaf(q.z, py, __builtin_fmaf(-q.w, px, -S.group[7]));
+    const float4 v = S.far[far_bin(x, y)];
+    const float b2 = __builtin_fmaf(x, x, y * y);
+    // (NaN where the square overflows: neither drops a point nor bounds)
+    lb = (b2 - __builtin_fmaf(v.x, x, v.y * y)) * __builtin_amdgcn_rsqf(b2) - v.z;
+    const float ex = x - v.x, ey = y - v.y;
+    ub = __builtin_amdgcn_sqrtf(__builtin_fmaf(ex, ex, ey * ey));
+}
+
 // Exact evaluation of one point by a row of 16 lanes, each with 1 / 16 of
 // the footprint in the pose's frame (the row's first lane returns the
 // distance).  The search queues a handful of points per pose, so what counts
@@ -221,6 +255,7 @@ template <int HB>
 struct EvalPoly {
     static constexpr int WAVES = HB <= 2 ? 6 : 4;  // per SIMD, without scratch in the loops
     static constexpr bool SCALED = true;           // PoseBounds::init_scaled
+    static constexpr bool EACH = false;            // has each()
     PolyPart<HB, EVAL_LANES> F;
     __device__ __forceinline__ void init(const float2* verts, const float4*, int n, int part, float4 q) {
         F.init(verts, part * HB, q.z, q.w);
@@ -253,6 +288,7 @@ template <int NB>
 struct EvalRect {
     static constexpr int WAVES = 6;
     static constexpr bool SCALED = false;
+    static constexpr bool EACH = true;
     float4 bx[NB];
     float c, s;
     __device__ __forceinline__ void init(const float2*, const float4* rects, int n, int part, float4 q) {
@@ -276,6 +312,14 @@ struct EvalRect {
         v = fminf(v, dpp_or<DPP_ROR1>(v, v));
         return v;
     }
+    // One point per lane, every box in turn.
+    static __device__ __forceinline__ float each(const float4* __restrict__ rects, int n, float4 q, float dx, float dy) {
+        const float px = __builtin_fmaf(q.z, dx, q.w * dy);
+        const float py = __builtin_fmaf(q.z, dy, -(q.w * dx));
+        float v = box_s(px, py, rects[0]);
+        for (int j = 1; j < n; ++j) v = fminf(v, box_s(px, py, rects[j]));
+        return v;
+    }
 };
 
 enum { CULL_ANY = 1, CULL_SCALED = 2 };  // a finite pose exists; one whose (cos, sin) is no rotation
@@ -295,7 +339,10 @@ __device__ __forceinline__ void cull_block(const CullArgs& A, const float2* __re
     const int wid = __builtin_amdgcn_readfirstlane(t / WAVE);
     CullWave& Wv = waves[wid];
     float4* leaf_vel = reinterpret_cast<float4*>(waves + nw);
-    int* queue_id = reinterpret_cast<int*>(leaf_vel + (MOVING ? CULL_LEAVES : 0)) + wid * CULL_QUEUE;
+    int* ids = reinterpret_cast<int*>(leaf_vel + (MOVING ? CULL_LEAVES : 0));
+    int* queue_id = ids + wid * CULL_QUEUE;
+    int* besti_of = ids + nw * CULL_QUEUE;  // CULL_POSES a wave
+    int* wave_besti = besti_of + wid * CULL_POSES;
     const FootTable& F = *A.foot;
     const int nv = *A.pts.n_valid;
     const int nleaf = (nv + LEAF_POINTS - 1) / LEAF_POINTS;
@@ -306,17 +353,32 @@ __device__ __forceinline__ void cull_block(const CullArgs& A, const float2* __re
     float2* lds_xy = reinterpret_cast<float2*>(S.leaf);
     static_assert(sizeof(float2) * POINTS_DIRECT_MAX <= sizeof(float4) * CULL_LEAVES, "the points fit the list");
 
+    // one lane: into the minimum of one of the wave's poses
+    auto merge = [&](int o, float d, int id) {
+        const float old = Wv.best[o];
+        if (ARGMIN) {
+            if (d < old || (d == old && d < INFINITY && id < wave_besti[o])) {
+                Wv.best[o] = d;
+                wave_besti[o] = id;
+            }
+        } else {
+            Wv.best[o] = fminf(old, d);
+        }
+    };
+
     // ---- poses, footprint table, the group's bounding circle
     {
         const uint4* src = reinterpret_cast<const uint4*>(&F + 1);
         const int n16 = (F.nx * F.ny + 3) / 4;
         for (int i = t; i < n16; i += nthreads) reinterpret_cast<uint4*>(cells)[i] = src[i];
+        if (t < FAR_BINS) S.far[t] = F.far[t];
         if (direct && !MOVING)
             for (int i = t; i < nv; i += nthreads) lds_xy[i] = A.pts.xy[i];
     }
     for (int tile = 0; tile < tiles; ++tile, g0 += gstep) {
     if (g0 >= A.npose) break;
     if (wid == 0) {
+        const int ln = opaque(lane);
         float xmin = INFINITY, xmax = INFINITY, ymin = INFINITY, ymax = INFINITY;  // maxima negated
         float tmin = INFINITY, tmax = INFINITY;
         bool any = false, scaled = false;
@@ -324,7 +386,7 @@ __device__ __forceinline__ void cull_block(const CullArgs& A, const float2* __re
         bool ok[CULL_WAVES * CULL_POSES / WAVE];
 #pragma unroll
         for (int k = 0; k < CULL_WAVES * CULL_POSES / WAVE; ++k) {
-            const int p = lane + k * WAVE, g = g0 + p;
+            const int p = ln + k * WAVE, g = g0 + p;
             ok[k] = false;
             if (p < nw * P) {
                 const bool live = g < A.npose;
@@ -337,7 +399,7 @@ __device__ __forceinline__ void cull_block(const CullArgs& A, const float2* __re
                 O.pose[o] = ok[k] ? q : make_float4(NAN, NAN, NAN, NAN);
                 O.tau[o] = tau;
                 O.best[o] = INFINITY;
-                O.besti[o] = -1;
+                if (ARGMIN) besti_of[p / P * CULL_POSES + o] = -1;
                 if (ok[k]) {
                     any = true;
                     // no rotation: the group's circles do not hold
@@ -375,12 +437,14 @@ __device__ __forceinline__ void cull_block(const CullArgs& A, const float2* __re
         if (lane == 0) {
             S.group[0] = gx;
             S.group[1] = gy;
-            // rounding of the centres (and of the moving points' positions) grows
-            // with the coordinates
-            S.group[2] = spread * 1.0001f + 2e-6f * (fabsf(gx) + fabsf(gy) + spread);
+            // rounding of the centres (2^-24 of each coordinate) and of the moving
+            // points' positions grows with the coordinates
+            S.group[2] = spread * 1.0001f + (MOVING ? 2e-6f : 5e-7f) * (fabsf(gx) + fabsf(gy) + spread);
             S.group[3] = tc;
             S.group[4] = ts * 1.0001f;
             S.group[5] = ta * 1.0001f;
+            S.group[6] = F.cx;
+            S.group[7] = F.cy;
             S.flags = fl;
             S.ub_super = S.ub_leaf = DKEY_INIT;
             S.n_super = S.n_leaf = 0;
@@ -400,7 +464,7 @@ __device__ __forceinline__ void cull_block(const CullArgs& A, const float2* __re
         const bool few = s1 - s0 <= 1 || direct;
         if (!few && !scaled) {
             float m = INFINITY;
-            for (int s = s0 + t; s < s1; s += nthreads) {
+            for (int s = s0 + opaque(t); s < s1; s += nthreads) {
                 const float4 c = A.pts.super[s];
                 const float dx = c.x - gx, dy = c.y - gy;
                 m = fminf(m, __builtin_sqrtf(dx * dx + dy * dy) + (c.z + c.w * ta) + hi_off);
@@ -414,7 +478,7 @@ __device__ __forceinline__ void cull_block(const CullArgs& A, const float2* __re
             if (!direct) __syncthreads();
             const float thr_s = scaled ? INFINITY : threshold(dkey_value(S.ub_super), slack);
             const int se = min(sb + CULL_SUPERS, s1);
-            for (int s = sb + t; s < se && !direct; s += nthreads) {
+            for (int s = sb + opaque(t); s < se && !direct; s += nthreads) {
                 bool keep = true;
                 if (!few && !scaled) {
                     const float4 c = A.pts.super[s];
@@ -429,7 +493,7 @@ __device__ __forceinline__ void cull_block(const CullArgs& A, const float2* __re
             if (!few && !scaled) {
                 float m = INFINITY;
                 for (int k = wid; k < ns; k += nw) {
-                    const int l = (sb + S.supers[k]) * SUPER_LEAVES + lane;
+                    const int l = (sb + S.supers[k]) * SUPER_LEAVES + opaque(lane);
                     if (l < nleaf) {
                         const float4 c = A.pts.leaf[l];
                         float x = c.x, y = c.y, r = 0.0f;
@@ -459,7 +523,7 @@ __device__ __forceinline__ void cull_block(const CullArgs& A, const float2* __re
                     const int kn = min(ns, k1 + (CULL_LEAVES - nlist) / SUPER_LEAVES);
                     if (kn == k1) break;
                     for (int k = k1 + wid; k < kn; k += nw) {
-                        const int l = (sb + S.supers[k]) * SUPER_LEAVES + lane;
+                        const int l = (sb + S.supers[k]) * SUPER_LEAVES + opaque(lane);
                         bool keep = l < nleaf;
                         float4 c = make_float4(0.f, 0.f, 0.f, 0.f), v = c;
                         if (keep) {
@@ -497,6 +561,7 @@ __device__ __forceinline__ void cull_block(const CullArgs& A, const float2* __re
                 float ub = INFINITY, pslack = slack, tau = 0.0f, apart = 1.0f;
                 float4 q = make_float4(0.f, 0.f, 1.f, 0.f);
                 PoseBounds B;
+                int far_min = 0;  // queued points of the pose that call for closer bounds
                 bool fresh = true;
                 while (pf < P) {
                     while (p < P) {
@@ -504,14 +569,15 @@ __device__ __forceinline__ void cull_block(const CullArgs& A, const float2* __re
                             q = wave_uniform(Wv.pose[p]);
                             tau = MOVING ? wave_uniform(Wv.tau[p]) : 0.0f;
                             pslack = slack + (MOVING ? 2e-6f * (fabsf(q.x) + fabsf(q.y)) : 0.0f);
-                            if (scaled)
+                            if (__builtin_expect(scaled, 0))
                                 pslack *= B.init_scaled<Eval::SCALED>(F, q.z, q.w, apart);
                             else
                                 B.init(F, q.z, q.w);
                             nkeep = 0;
                             c0 = 0;
                             nq0 = nq;
-                            if (lane == 0) Wv.begin[p] = nq;
+                            far_min = scaled ? CULL_QUEUE : CULL_FAR;
+                            if (lane == 0) Wv.begin[p] = static_cast<unsigned short>(nq);
                             if (direct) {
                                 fresh = false;
                                 ub = signed_sqrt_fast(Wv.best[p]);
@@ -519,7 +585,7 @@ __device__ __forceinline__ void cull_block(const CullArgs& A, const float2* __re
                             }
                             if (!(q.x == q.x)) {
                                 // no finite distance
-                                if (lane == 0) Wv.end[p] = nq;
+                                if (lane == 0) Wv.end[p] = static_cast<unsigned short>(nq);
                                 ++p;
                                 fresh = true;
                                 continue;
@@ -565,6 +631,38 @@ __device__ __forceinline__ void cull_block(const CullArgs& A, const float2* __re
                                 }
                             wave_lds_fence();
                             fresh = false;
+                            if (__builtin_expect(nkeep > CULL_FAR_LEAVES && far_min < CULL_QUEUE, 0)) {
+                                // most are far away, where the table's bounds
+                                // say little: the closer ones
+                                // (the pose again: it need not stay in registers)
+                                const float4 qc = Wv.pose[p];
+                                auto bounds = [&](int i, float& lb, float& u) {
+                                    const float4 c = S.leaf[Wv.leaf[i]];
+                                    float x = c.x, y = c.y, r = c.z;
+                                    if (MOVING) {
+                                        const float4 v = leaf_vel[Wv.leaf[i]];
+                                        x = __builtin_fmaf(v.x, tau, x);
+                                        y = __builtin_fmaf(v.y, tau, y);
+                                        r = __builtin_fmaf(v.z, fabsf(tau - v.w), r);
+                                    }
+                                    far_bounds(S, qc, x - qc.x, y - qc.y, lb, u);
+                                    lb -= r;
+                                };
+                                const int n = nkeep;
+                                nkeep = 0;
+                                for (int b = 0; b < n; b += WAVE) {
+                                    const int i = b + opaque(lane);
+                                    float lb, u;
+                                    bounds(min(i, n - 1), lb, u);
+                                    const unsigned short l = Wv.leaf[min(i, n - 1)];
+                                    ub = fminf(ub, wave_min(u));
+                                    const bool keep = i < n && !(lb > threshold(ub, pslack));
+                                    const unsigned long long mask = __ballot(keep);
+                                    if (keep) Wv.leaf[nkeep + lanes_below(mask)] = l;
+                                    nkeep += __popcll(mask);
+                                    wave_lds_fence();
+                                }
+                            }
                         }
                         // the points of the kept leaves, CULL_CHUNK batches of 64
                         // bounded before they are filtered
@@ -651,7 +749,67 @@ __device__ __forceinline__ void cull_block(const CullArgs& A, const float2* __re
                                 nq += __popcll(mask);
                             }
                         }
-                        if (lane == 0) Wv.end[p] = nq;
+                        if (__builtin_expect(nq - nq0 > far_min, 0)) {
+                            // still many: the closer bounds of far points
+                            wave_lds_fence();
+                            const float4 qc = Wv.pose[p];
+                            const int n = nq;
+                            nq = nq0;
+                            for (int b = nq0; b < n; b += WAVE) {
+                                const int i = b + opaque(lane);
+                                const float2 o = Wv.queue[min(i, n - 1)];
+                                const int id = ARGMIN ? queue_id[min(i, n - 1)] : 0;
+                                float lb, u;
+                                far_bounds(S, qc, o.x - qc.x, o.y - qc.y, lb, u);
+                                ub = fminf(ub, wave_min(u));
+                                const bool keep = i < n && !(lb > threshold(ub, pslack));
+                                const unsigned long long mask = __ballot(keep);
+                                if (keep) {
+                                    const int to = nq + static_cast<int>(lanes_below(mask));
+                                    Wv.queue[to] = o;
+                                    if (ARGMIN) queue_id[to] = id;
+                                }
+                                nq += __popcll(mask);
+                                wave_lds_fence();
+                            }
+                            if (4 * (nq - nq0) > 3 * (n - nq0)) far_min = CULL_QUEUE;  // of no use here
+                            if (full && nq + CULL_CHUNK * WAVE <= CULL_QUEUE) continue;  // with the pose's other points
+                        }
+                        if constexpr (Eval::EACH)
+                            if (__builtin_expect(nq - nq0 >= CULL_EACH, 0)) {
+                                // many: one per lane costs 10 instructions a box
+                                // for 64 of them (the row's 80 for 4)
+                                wave_lds_fence();
+                                const float4 qc = Wv.pose[p];
+                                float best = INFINITY;
+                                int besti = 0x7FFFFFFF;
+                                const int ln = opaque(lane);
+                                for (int b = nq0; b < nq; b += WAVE) {
+                                    // (lanes past the end take the last point again)
+                                    const int i = min(b + ln, nq - 1);
+                                    const float2 o = Wv.queue[i];
+                                    const float sd = Eval::each(rects, nprim, qc, o.x - qc.x, o.y - qc.y);
+                                    if (ARGMIN) {
+                                        const int id = queue_id[i];
+                                        if (sd < best || (sd == best && id < besti)) {
+                                            best = sd;
+                                            besti = id;
+                                        }
+                                    } else {
+                                        best = fminf(best, sd);
+                                    }
+                                }
+                                const float d = wave_min(best);
+                                if (ARGMIN) besti = static_cast<int>(wave_umin(best == d ? static_cast<unsigned>(besti) : ~0u));
+                                if (ln == 0) merge(p, d, besti);
+                                wave_lds_fence();
+                                nq = nq0;
+                                if (full && nq + CULL_CHUNK * WAVE <= CULL_QUEUE) {
+                                    ub = fminf(ub, signed_sqrt_fast(Wv.best[p]));
+                                    continue;  // with the pose's other points
+                                }
+                            }
+                        if (lane == 0) Wv.end[p] = static_cast<unsigned short>(nq);
                         if (full) break;
                         ++p;
                         fresh = true;
@@ -704,17 +862,7 @@ __device__ __forceinline__ void cull_block(const CullArgs& A, const float2* __re
                                     best = fminf(best, ob);
                                 }
                             }
-                            if (slot < np && (ln & (per - 1)) == 0) {
-                                const float old = Wv.best[pp];
-                                if (ARGMIN) {
-                                    if (best < old || (best == old && best < INFINITY && besti < Wv.besti[pp])) {
-                                        Wv.best[pp] = best;
-                                        Wv.besti[pp] = besti;
-                                    }
-                                } else {
-                                    Wv.best[pp] = fminf(old, best);
-                                }
-                            }
+                            if (slot < np && (ln & (per - 1)) == 0) merge(pp, best, besti);
                         }
                     wave_lds_fence();
                     // a pose cut by the full queue goes on with its exact
@@ -735,11 +883,11 @@ __device__ __forceinline__ void cull_block(const CullArgs& A, const float2* __re
         }
     }
     wave_lds_fence();
-    const int g = g0 + wid * P + lane;
-    if (lane < P && g < A.npose) {
-        const float b = Wv.best[lane];
+    const int ln = opaque(lane), g = g0 + wid * P + ln;
+    if (ln < P && g < A.npose) {
+        const float b = Wv.best[ln];
         if (ARGMIN) {
-            const int i = Wv.besti[lane];
+            const int i = wave_besti[ln];
             const unsigned idx = i < 0 ? 0xFFFFFFFFu : static_cast<unsigned>(i);
             atomicMin(&A.key64[g], (static_cast<unsigned long long>(dkey(b)) << 32) | idx);
         } else {

@@ -93,7 +93,12 @@ hipError_t launch_points(const float* x, const float* y, const float* vx, const 
 // bound is positive; a point outside projects onto the grid's rectangle,
 // which is convex, so with the distance a to the projection and the
 // projection's bounds [lb, ub] its distance lies in
-// [sqrt(lb^2 + a^2), ub + a].
+// [sqrt(lb^2 + a^2), ub + a].  That interval is as wide as the margin; far[k]
+// bounds points outside closely: in directions u (from the box's centre) of
+// the k-th of FAR_BINS intervals of the pseudo-angle (far_bin), the footprint
+// reaches at most v . u + eps, where v is one of its corners, so the distance
+// of a point b at |b| u lies in [|b| - v . u - eps, |b - v|].
+constexpr int FAR_BINS = 64;
 struct FootTable {
     float cx, cy;      // centre of the bounding box
     float radius;      // of a circle around (cx, cy) that holds the footprint
@@ -105,14 +110,16 @@ struct FootTable {
     float base, quantum, err_cell, err_linear;
     int nx, ny;
     int pad_[15];
+    float4 far[FAR_BINS];  // v (from the centre), eps, unused
 };
-static_assert(sizeof(FootTable) == 128, "the cells start 128 bytes into the buffer");
+static_assert(sizeof(FootTable) == 128 + 16 * FAR_BINS, "the cells start on 128 bytes of the buffer");
 constexpr int FOOT_CELLS = 4096;  // most cells of a table (16 KB of LDS)
 inline size_t foot_table_bytes() { return sizeof(FootTable) + sizeof(uint32_t) * FOOT_CELLS; }
-// Fill the cells of the table at `table` (its head is already there) from
-// the point-wise tables of the footprint (launch_sdf_points).
+// Fill the cells and far[] of the table at `table` (its head is already there) from
+// the point-wise tables of the footprint (launch_sdf_points) and a polygon's
+// vertices.
 hipError_t launch_foot_table(int kind, FootTable* table, const float4* tab_a, const float4* tab_b,
-                             int count, hipStream_t s);
+                             const float2* verts, int count, hipStream_t s);
 
 // Time of pose g for moving points: h = (g / div) % mod, t = (h + off) dt.
 struct PoseTime {

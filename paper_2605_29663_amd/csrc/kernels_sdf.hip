@@ -23,6 +23,44 @@ void k_dmin(CullArgs A, int P, int tiles, int supers, const float2* __restrict__
                                      s0 + supers, lds);
 }
 
+// Direction of the pseudo-angle a in [-1, 3) (far_bin).
+__device__ __forceinline__ float2 far_dir(float a) {
+    const float x = a <= 1.0f ? 1.0f - fabsf(a) : fabsf(a - 2.0f) - 1.0f, y = a <= 1.0f ? a : 2.0f - a;
+    const float r = 1.0f / __builtin_sqrtf(x * x + y * y);
+    return make_float2(x * r, y * r);
+}
+
+// FootTable::far[k] from the polygon's vertices or the boxes: v reaches furthest in the bin's middle; eps is the most that
+// another corner reaches beyond it in the bin, widened for the rounding of
+// far_bin.  w . u is a cosine of u's angle: over the bin it is largest at an
+// end, or |w| if w's direction is inside.
+__device__ float4 far_entry(int kind, const FootTable& F, int k, const float2* __restrict__ verts,
+                            const float4* __restrict__ rects, int count) {
+    constexpr float STEP = 4.0f / FAR_BINS;
+    const float2 m = far_dir((k + 0.5f) * STEP - 1.0f), e0 = far_dir((k - 0.01f) * STEP - 1.0f),
+                 e1 = far_dir((k + 1.01f) * STEP - 1.0f);
+    auto corner = [&](int i) {
+        if (kind == 0) return make_float2(verts[i].x - F.cx, verts[i].y - F.cy);
+        const float4 a = rects[i >> 2];
+        return make_float2(a.x + (i & 1 ? a.z : -a.z) - F.cx, a.y + (i & 2 ? a.w : -a.w) - F.cy);
+    };
+    const int n = kind == 0 ? count : 4 * count;
+    float2 v = corner(0);
+    for (int i = 1; i < n; ++i) {
+        const float2 w = corner(i);
+        if (w.x * m.x + w.y * m.y > v.x * m.x + v.y * m.y) v = w;
+    }
+    float eps = 0.0f;
+    for (int i = 0; i < n; ++i) {
+        float2 w = corner(i);
+        w.x -= v.x;
+        w.y -= v.y;
+        eps = fmaxf(eps, fmaxf(w.x * e0.x + w.y * e0.y, w.x * e1.x + w.y * e1.y));
+        if (e0.x * w.y - e0.y * w.x > 0.0f && w.x * e1.y - w.y * e1.x > 0.0f) eps = fmaxf(eps, __builtin_sqrtf(w.x * w.x + w.y * w.y));
+    }
+    return make_float4(v.x, v.y, eps + 1e-5f * F.reach, 0.0f);
+}
+
 // Cells of a footprint's bound table (FootTable), one thread each.  r: a bit
 // more than half the cell's diagonal; a feature further from the centre than
 // the nearest by more than 2 r is nearest nowhere in the cell.  Three kinds:
@@ -38,9 +76,14 @@ void k_dmin(CullArgs A, int P, int tiles, int supers, const float2* __restrict__
 // The second kind takes the search from 94 to 75 us a launch on average at 8192
 // corridor points and 16 vertices (the fill itself is a set-up cost).
 __global__ __launch_bounds__(256) void k_foot_table(int kind, const FootTable* __restrict__ F,
-                                                    uint32_t* __restrict__ cells,
+                                                    uint32_t* __restrict__ cells, float4* __restrict__ far,
                                                     const float4* __restrict__ ta,
-                                                    const float4* __restrict__ tb, int count) {
+                                                    const float4* __restrict__ tb,
+                                                    const float2* __restrict__ verts, int count) {
+    if (blockIdx.x == FOOT_CELLS / 256) {
+        if (threadIdx.x < FAR_BINS) far[threadIdx.x] = far_entry(kind, *F, static_cast<int>(threadIdx.x), verts, ta, count);
+        return;
+    }
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= F->nx * F->ny) return;
     const float x = (static_cast<float>(c % F->nx) + 0.5f - F->ox) * F->dx;
@@ -297,9 +340,9 @@ hipError_t launch_sdf_points(int kind, const float* px, const float* py, int n,
 }
 
 hipError_t launch_foot_table(int kind, FootTable* table, const float4* tab_a, const float4* tab_b,
-                             int count, hipStream_t s) {
-    hipLaunchKernelGGL(k_foot_table, dim3(FOOT_CELLS / 256), dim3(256), 0, s, kind, table,
-                       reinterpret_cast<uint32_t*>(table + 1), tab_a, tab_b, count);
+                             const float2* verts, int count, hipStream_t s) {
+    hipLaunchKernelGGL(k_foot_table, dim3(FOOT_CELLS / 256 + 1), dim3(256), 0, s, kind, table,
+                       reinterpret_cast<uint32_t*>(table + 1), table->far, tab_a, tab_b, verts, count);
     return hipGetLastError();
 }
 
