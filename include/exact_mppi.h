@@ -98,7 +98,7 @@ typedef struct mppi_params {
  * context, see mppi_batch_create: bit-identical results, fewer launch
  * overheads, the persistent distance kernel).  The first step of a
  * parameter set builds the batch and autotunes its item size
- * (mppi_batch_autotune: about 70 launches of the distance pass); the graph
+ * (mppi_batch_autotune: about 80 launches of the distance pass); the graph
  * is rebuilt when the parameters change and re-planned when points or
  * footprint change.  With profiling on (mppi_set_profiling) the batch runs
  * eagerly and mppi_get_profile reports its distance pass.  The call first
@@ -375,13 +375,15 @@ MPPI_API int mppi_batch_refresh(mppi_batch b);
 MPPI_API int mppi_step_batched(mppi_batch b, const float* q0, float* dU, const uint64_t* seeds,
                                const uint64_t* steps, float* u_out, int* valid_out, int use_graph);
 
-/* Tile autotuner of the batch (for its scenes of few points; the bounded search
- * of the others has a fixed plan): after a warm-up, times the persistent
- * signed-distance pass for queue items of 2^16 .. 2^26 point-primitive pairs
+/* Tile autotuner of the batch: after a warm-up, times the signed-distance pass
+ * of the default plan and of queue items of 2^16 .. 2^26 point-primitive pairs
  * (reps launches each, HIP events, a forward and a backward sweep, the
- * faster of the two kept) and re-plans with the fastest.
- * *out_work_per_item (may be NULL) receives it.  Results do not depend on
- * the choice.  Synchronous.                                                 */
+ * faster of the two kept) and re-plans with the fastest.  An item of a scene
+ * that takes the bounded search holds the poses whose pairs with all its points
+ * make that number; by default as many as fill the chip once, at most 128.
+ * *out_work_per_item (may be NULL) receives the pairs per item of the plan (see
+ * mppi_batch_info; the default plan's where that is the fastest).  Results do
+ * not depend on the choice.  Synchronous.                                   */
 MPPI_API int mppi_batch_autotune(mppi_batch b, int reps, double* out_work_per_item);
 
 /* Fix the queue item size: work_per_item point-primitive pairs per item
