@@ -646,16 +646,15 @@ int mppi_autotune(mppi_ctx ctx, const mppi_params* prm, int reps, int* out_block
     // chunk counts that the pass can take: ranges of the hierarchy, or (every
     // point) chunks of at least 32 points, 8 when there are few poses (the pass
     // then needs the point chunks to fill the chip)
-    const bool every = dmin_every(padded, ctx->n_points);
-    auto usable = [&](int nc, int min_chunk) {
-        if (every) return nc == 1 || ctx->n_points / nc >= min_chunk;
+    auto usable = [&](int poses, int nc, int min_chunk) {
+        if (dmin_every(padded, ctx->n_points, poses, ctx->moving)) return nc == 1 || ctx->n_points / nc >= min_chunk;
         int supers, ranges;
         dmin_ranges(ctx->n_points, nc, supers, ranges);
         return ranges == nc;
     };
     for (int b : blocks)
         for (int nc : chunk_counts)
-            if (usable(nc, npose <= 16384 ? 8 : 32)) cand.emplace_back(b, nc);
+            if (usable(npose, nc, npose <= 16384 ? 8 : 32)) cand.emplace_back(b, nc);
     std::vector<float> best(cand.size(), 1e30f);
     unsigned int* key = ctx->key.as<unsigned int>();
     int rc = MPPI_OK;
@@ -701,7 +700,7 @@ int mppi_autotune(mppi_ctx ctx, const mppi_params* prm, int reps, int* out_block
         const int nchunks[] = {1, 2, 4, 8, 16, 32, 64, 128, 256, 512, 1024};
         std::vector<int> vc;
         for (int nc : nchunks)
-            if (usable(nc, 8)) vc.push_back(nc);
+            if (usable(A.T, nc, 8)) vc.push_back(nc);
         std::vector<float> vbest(vc.size(), 1e30f);
         const PoseTime ptn{1, A.T, A.state_offset, A.dt};
         HIP_TRY(ctx, ctx->key_nom.ensure(sizeof(unsigned int) * A.T));
@@ -729,7 +728,7 @@ int mppi_autotune(mppi_ctx ctx, const mppi_params* prm, int reps, int* out_block
             size_t bi = 0;
             for (size_t ci = 1; ci < vc.size(); ++ci)
                 if (vbest[ci] < vbest[bi]) bi = ci;
-            tune(A.T, every || vc[bi] > 1 ? 64 : 0, vc[bi]);
+            tune(A.T, dmin_every(padded, ctx->n_points, A.T, ctx->moving) || vc[bi] > 1 ? 64 : 0, vc[bi]);
         }
     }
     (void)hipEventDestroy(e0);

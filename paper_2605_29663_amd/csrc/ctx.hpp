@@ -317,7 +317,7 @@ inline DminLaunch dmin_launch(mppi_ctx ctx, const float4* poses, int npose, Pose
                               unsigned int* key, unsigned long long* key64, int force_block = 0,
                               int force_nchunk = 0) {
     const int padded = kind == 0 ? ctx->BP : ctx->RP;
-    const bool every = emppi::dmin_every(padded, ctx->n_points);
+    const bool every = emppi::dmin_every(padded, ctx->n_points, npose, ctx->moving);
     int block = 0, nchunk = 1, chunk = 0;  // block 0: the default shape
     if (every) choose_tiles(kind, padded, npose, ctx->n_points, block, nchunk, chunk);
     const auto it = ctx->tuned.find(std::make_tuple(kind, padded, ctx->moving ? 1 : 0, npose, ctx->n_points));

@@ -148,14 +148,22 @@ __device__ __forceinline__ float dkey_distance(unsigned int k) {
     return sq < 0.0f ? -__builtin_sqrtf(-sq) : __builtin_sqrtf(sq);
 }
 
-// The distance pass evaluates every point (kernels_sdf_every.hip) of sets
-// that keep the caller's order while that takes fewer instructions than the
-// bounded search (cull_device.hpp): (10.75 padded + 6) / 64 per point and pose
-// against about 600 per pose at 512 points (measured at 512 points, 5120
-// poses, 8 vertices: 9.6 against 14.5 us; the sets' sizes where the two meet
-// follow 1 / vertices).
-inline bool dmin_every(int padded, int n_points) {
-    return n_points <= POINTS_DIRECT_MAX && n_points * (10.75 * padded + 6.0) <= 50000.0;
+// The distance pass evaluates every point (kernels_sdf_every.hip) where that is
+// faster than the bounded search (cull_device.hpp): (10.75 padded + 6) / 64
+// instructions per pose and point, against about 1000 per pose (static sets; up
+// to 4000 moving ones) and some 6 us more for the search's chain of phases, which
+// weigh the more the fewer poses there are.  Microseconds, every point / search,
+// of 1280, 5120 and 81920 poses: 4 edges, 1000 points 8 / 12, 11 / 16, 69 / 82,
+// 2000 points 12 / 12, 17 / 15, 129 / 73; 16 edges, 300 points 10 / 10, 14 / 14,
+// 85 / 72, 600 points 11 / 12, 20 / 16, 152 / 77; moving, 8 edges, 1000 points
+// 12 / 16, 18 / 27, 132 / 210, 16 edges, 600 points 11 / 15, 21 / 25, 158 / 157.
+// Above 16 primitives a lane's share of the work is too long a chain for few
+// poses (32 edges, 300 points: 12 / 10, 22 / 14).
+constexpr int EVERY_MAX_POINTS = 2048;
+inline bool dmin_every(int padded, int n_points, long long npose, bool moving) {
+    double limit = 50000.0;
+    if (padded <= 16) limit = npose <= 2048 ? 100000.0 : moving ? 80000.0 : npose <= 8192 ? 60000.0 : limit;
+    return n_points <= EVERY_MAX_POINTS && n_points * (10.75 * padded + 6.0) <= limit;
 }
 
 // One launch of the fused transform + signed distance + min-over-points

@@ -151,7 +151,7 @@ __global__ __launch_bounds__(VAL_SMALL_THREADS) void k_validate_small(
                 for (int i = j; i < tn; i += S) {
                     float dx, dy;
                     point_rel<MOVING>(tile, i, tau, q.x, q.y, dx, dy);
-                    take<false>(F.eval(dx, dy), t0 + i, best, besti);
+                    take<false>(F.eval(dx, dy), t0 + i, nullptr, best, besti);
                 }
         }
     } else {
@@ -171,7 +171,7 @@ __global__ __launch_bounds__(VAL_SMALL_THREADS) void k_validate_small(
                     float sv = box_s(px, py, bx[0]);
 #pragma unroll
                     for (int k = 1; k < PAD; ++k) sv = fminf(sv, box_s(px, py, bx[k]));
-                    take<false>(sv, t0 + i, best, besti);
+                    take<false>(sv, t0 + i, nullptr, best, besti);
                 }
         }
     }

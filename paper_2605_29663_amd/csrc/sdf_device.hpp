@@ -210,11 +210,12 @@ __device__ __forceinline__ int for_point_pairs(const float* lds, int tn, Fn&& f)
     return i;
 }
 
-// Running min (and lowest-index argmin: points arrive in increasing index).
+// Running min and argmin: of equal minima the point of lowest caller's index
+// (idx; the points of a sorted set arrive in no order of theirs).
 template <bool ARGMIN>
-__device__ __forceinline__ void take(float s, int i, float& best, int& besti) {
+__device__ __forceinline__ void take(float s, int i, const int* __restrict__ idx, float& best, int& besti) {
     if (ARGMIN) {
-        if (s < best) {
+        if (s <= best && (s < best || (besti >= 0 && idx[i] < idx[besti]))) {
             best = s;
             besti = i;
         }
@@ -386,14 +387,14 @@ __device__ __forceinline__ void dmin_poly_range(float4 q, float tau, const Point
                 pair_rel<MOVING>(p, tau, q.x, q.y, dx0, dy0, dx1, dy1);
                 const float s0 = F.eval(dx0, dy0);
                 const float s1 = F.eval(dx1, dy1);
-                take<ARGMIN>(s0, t0 + k, best, besti);
-                take<ARGMIN>(s1, t0 + k + 1, best, besti);
+                take<ARGMIN>(s0, t0 + k, pts.idx, best, besti);
+                take<ARGMIN>(s1, t0 + k + 1, pts.idx, best, besti);
             });
         }
         for (; i < tn; ++i) {
             float dx, dy;
             point_rel<MOVING>(lds, i, tau, q.x, q.y, dx, dy);
-            take<ARGMIN>(F.eval(dx, dy), t0 + i, best, besti);
+            take<ARGMIN>(F.eval(dx, dy), t0 + i, pts.idx, best, besti);
         }
     }
 }
@@ -421,15 +422,15 @@ __device__ __forceinline__ void dmin_poly_part_range(float4 q, float tau, const 
             pair_rel<MOVING>(p, tau, q.x, q.y, dx0, dy0, dx1, dy1);
             F.eval(dx0, dy0, m0, o0);
             F.eval(dx1, dy1, m1, o1);
-            take<ARGMIN>(part_combine<L>(m0, o0), t0 + k, best, besti);
-            take<ARGMIN>(part_combine<L>(m1, o1), t0 + k + 1, best, besti);
+            take<ARGMIN>(part_combine<L>(m0, o0), t0 + k, pts.idx, best, besti);
+            take<ARGMIN>(part_combine<L>(m1, o1), t0 + k + 1, pts.idx, best, besti);
         });
         if (i < tn) {
             float dx, dy, m;
             unsigned long long o;
             point_rel<MOVING>(lds, i, tau, q.x, q.y, dx, dy);
             F.eval(dx, dy, m, o);
-            take<ARGMIN>(part_combine<L>(m, o), t0 + i, best, besti);
+            take<ARGMIN>(part_combine<L>(m, o), t0 + i, pts.idx, best, besti);
         }
     }
 }
@@ -461,13 +462,13 @@ __device__ __forceinline__ void dmin_rect_range(float4 q, float tau, const Point
         const int i = for_point_pairs<MOVING>(lds, tn, [&](const PointPair<MOVING>& p, int k) {
             float dx0, dy0, dx1, dy1;
             pair_rel<MOVING>(p, tau, q.x, q.y, dx0, dy0, dx1, dy1);
-            take<ARGMIN>(eval(dx0, dy0), t0 + k, best, besti);
-            take<ARGMIN>(eval(dx1, dy1), t0 + k + 1, best, besti);
+            take<ARGMIN>(eval(dx0, dy0), t0 + k, pts.idx, best, besti);
+            take<ARGMIN>(eval(dx1, dy1), t0 + k + 1, pts.idx, best, besti);
         });
         if (i < tn) {
             float dx, dy;
             point_rel<MOVING>(lds, i, tau, q.x, q.y, dx, dy);
-            take<ARGMIN>(eval(dx, dy), t0 + i, best, besti);
+            take<ARGMIN>(eval(dx, dy), t0 + i, pts.idx, best, besti);
         }
     }
 }

@@ -1,0 +1,73 @@
+"""Small sets and few poses on both sides of the rule that picks between every
+point and the search: same distances and argmin, and no slower than before the
+search existed."""
+import numpy as np
+import pytest
+
+from paper_2605_29663_amd import scenes
+from test_gpu_search import _footprint, _poses
+
+pytestmark = pytest.mark.gpu
+
+
+# sorted sets (above 512 points) that are evaluated point by point at few poses
+# and searched at many: repeated points, so that ties are decided
+@pytest.mark.parametrize("n,prims", [(513, 3), (513, 16), (900, 8), (1100, 8), (2048, 4), (2049, 4), (1500, -1),
+                                     (600, -12), (740, -12)])
+@pytest.mark.parametrize("poses", [1, 40, 2048, 2049, 9000])
+@pytest.mark.parametrize("moving", [False, True])
+def test_rule_changes_no_result(n, prims, poses, moving):
+    import torch
+    import paper_2605_29663_amd as pkg
+    rng = np.random.default_rng(n + abs(prims) + poses)
+    kind, geom = _footprint(rng, prims)
+    ctx = pkg.Context(0)
+    ctx.set_footprint(kind, geom)
+    x, y = rng.uniform(-4, 4, (2, n)).astype(np.float32)
+    vx, vy = (rng.uniform(-1, 1, (2, n)) * (rng.random(n) < 0.4)).astype(np.float32)
+    for a in (x, y, vx, vy):
+        a[n // 2:n // 2 + 200] = a[:200]
+        a[n - 50:] = a[:50]
+    P = torch.tensor(_poses(rng, poses, 1, 1.0), device="cuda")
+
+    def run(sl):
+        ctx.set_points(x[sl], y[sl], vx[sl] if moving else None, vy[sl] if moving else None)
+        d, a = ctx.sdf_min_poses(P, dt=0.2, state_offset=1, kind=kind, argmin=True)
+        assert torch.equal(d, ctx.sdf_min_poses(P, dt=0.2, state_offset=1, kind=kind))
+        return d.cpu().numpy(), a.cpu().numpy()
+
+    d, a = run(slice(0, n))
+    ref, arg = np.full(d.shape, np.inf, np.float32), np.full(d.shape, -1)
+    for i in range(0, n, 100):  # sets in the caller's order
+        di, ai = run(slice(i, min(i + 100, n)))
+        less = di < ref
+        ref, arg = np.where(less, di, ref), np.where(less, ai + i, arg)
+    np.testing.assert_array_equal(d, ref)
+    np.testing.assert_array_equal(a, arg)
+    ctx.close()
+
+
+@pytest.mark.parametrize("K,T,N,prims,us", [(512, 16, 700, -2, 10.0), (256, 20, 1000, 4, 13.5), (64, 20, 600, 3, 9.5)])
+def test_small_steps_evaluate_every_point(K, T, N, prims, us):
+    """The distance pass of small steps (with its timing events about 9 / 11 / 7 us;
+    the search takes 15 / 16 / 12)."""
+    import torch
+    import paper_2605_29663_amd as pkg
+    rng = np.random.default_rng(7)
+    kind, geom = _footprint(rng, prims)
+    ctx = pkg.Context(0)
+    ctx.set_footprint(kind, geom)
+    x, y = rng.uniform(1.5, 3, (2, N)) * rng.choice([-1, 1], (2, N))
+    ctx.set_points(x.astype(np.float32), y.astype(np.float32))
+    prm = scenes.params("c1", K=K, T=T, footprint_kind=kind, validate=0)
+    U = torch.zeros((T, 2), device="cuda")
+    best = np.inf
+    for _ in range(6):
+        ctx.mppi_set_profiling(True)
+        for _ in range(10):
+            ctx.mppi_step(prm, np.zeros(3, np.float32), U, 1, 0)
+        ms, n = ctx.mppi_get_profile()
+        best = min(best, 1e3 * ms / n)
+    print(best)
+    assert best < us
+    ctx.close()
