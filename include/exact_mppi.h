@@ -380,7 +380,7 @@ MPPI_API int mppi_step_batched(mppi_batch b, const float* q0, float* dU, const u
  * (reps launches each, HIP events, a forward and a backward sweep, the
  * faster of the two kept) and re-plans with the fastest.  An item of a scene
  * that takes the bounded search holds the poses whose pairs with all its points
- * make that number; by default as many as fill the chip once, at most 128.
+ * make that number (by default at most 128).
  * *out_work_per_item (may be NULL) receives the pairs per item of the plan (see
  * mppi_batch_info; the default plan's where that is the fastest).  Results do
  * not depend on the choice.  Synchronous.                                   */

@@ -264,17 +264,20 @@ int plan(mppi_batch b, double work_target) {
             if (!every(s)) {
                 // bounded search: the poses an item takes from the requested
                 // work per item (its pairs, as if every point were evaluated);
-                // by default so that the batch fills the chip's wave slots
-                // once, at most a tile of 128: with up to 512 (4 tiles to one
-                // load of the footprint's table) the last items of a scene
-                // leave compute units idle (64 scenes 6670 us a step against
-                // 6040, 8 scenes 1220 against 892, 3 scenes of 3000 points 374
-                // against 354).  Validation: one pose per wave.
+                // by default so that the batch fills the chip's wave slots a
+                // whole number of times with items of at most a tile of 128:
+                // with one fill of up to 512 poses an item (4 tiles to one load
+                // of the footprint's table) the last items leave compute units
+                // idle (64 scenes 6670 us a step against 6040, 8 scenes 1220
+                // against 880, 3 scenes of 3000 points 374 against 360), and 1.1
+                // fills take longer than two (one scene 342 against 304).
+                // Validation: one pose per wave.
                 const double pairs = static_cast<double>(std::max(c->n_points, 1)) * padded;
+                constexpr double TILE = SEARCH_WAVES * DMIN_MAX_POSES;
                 double want = static_cast<double>(search_poses) / (256.0 * 24.0) * SEARCH_WAVES;
-                if (work_target > 0.0) want = work_per_item / pairs;
-                const int n = pass == 1 ? SEARCH_WAVES
-                                        : static_cast<int>(std::min(1.0 * SEARCH_WAVES * DMIN_MAX_POSES, std::max(want, 1.0 * SEARCH_WAVES)));
+                want /= std::ceil(std::max(want, 1.0) / TILE);
+                if (work_target > 0.0) want = std::min(512.0, work_per_item / pairs);
+                const int n = pass == 1 ? SEARCH_WAVES : static_cast<int>(std::max(std::ceil(want), 1.0 * SEARCH_WAVES));
                 const int per_wave = (n + SEARCH_WAVES - 1) / SEARCH_WAVES;
                 const int tiles = (per_wave + DMIN_MAX_POSES - 1) / DMIN_MAX_POSES;
                 const int pw = (per_wave + tiles - 1) / tiles;
