@@ -296,16 +296,16 @@ MPPI_API int mppi_step(mppi_ctx ctx, const mppi_params* prm, const float* q0, fl
 
 /* Tile-shape autotuner for the fused transform + signed distance + min
  * stage of mppi_step: for prm's shape and the footprint and points currently
- * set, time every candidate (the default rule, and workgroup sizes in {64,
+ * set, time every candidate (the default shape, and workgroup sizes in {64,
  * 128, 256} poses with numbers of point chunks; the bounded search of larger
- * sets reads the first as poses per workgroup and splits only sets above 32768
- * points) on one sampled step with HIP events (reps launches each) and keep the
- * fastest for this context; mppi_step then uses it whenever the
- * shape (kind, padded primitive count, moving points, K*T, N) matches.  With
- * prm->validate the point-chunk count of the validation pass (T poses) is
- * tuned the same way.  out_block / out_nchunk (host, may be NULL) receive
- * the sampled pass's choice (0, 0: the default rule).  Results do not depend on
- * the choice (bit-identical).  Synchronous.                                            */
+ * sets reads the first as poses per workgroup, 64 standing for its own rule,
+ * and splits only sets above 32768 points) on one sampled step with HIP events
+ * (reps launches each) and keep the fastest for this context; mppi_step then
+ * uses it whenever the shape (kind, padded primitive count, moving points, K*T,
+ * N) matches.  With prm->validate the point-chunk count of the validation pass
+ * (T poses) is tuned the same way.  out_block / out_nchunk (host, may be NULL)
+ * receive the sampled pass's choice, as mppi_set_tiles takes it.  Results do not
+ * depend on the choice (bit-identical).  Synchronous.                       */
 MPPI_API int mppi_autotune(mppi_ctx ctx, const mppi_params* prm, int reps, int* out_block,
                            int* out_nchunk);
 
@@ -317,7 +317,8 @@ MPPI_API int mppi_tune_get(mppi_ctx ctx, char* buf, int len);
 MPPI_API int mppi_tune_set(mppi_ctx ctx, const char* text);
 
 /* Fix the tile shape of every fused signed-distance launch of this context
- * (block = poses per workgroup: 64, 128 or 256; nchunk = point chunks, >= 1);
+ * (block = poses per workgroup: 64, 128 or 256, of which 64 leaves the bounded
+ * search its own rule; nchunk = point chunks, >= 1);
  * block = 0 returns to the autotuned / default shapes.  Results are
  * bit-identical for every shape; this exists for tests and experiments.   */
 MPPI_API int mppi_set_tiles(mppi_ctx ctx, int block, int nchunk);

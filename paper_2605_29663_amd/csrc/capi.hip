@@ -630,19 +630,17 @@ int mppi_autotune(mppi_ctx ctx, const mppi_params* prm, int reps, int* out_block
     hipEvent_t e0, e1;
     HIP_TRY(ctx, hipEventCreate(&e0));
     HIP_TRY(ctx, hipEventCreate(&e1));
-    // block 0: the default shape, which needs no entry
     auto tune = [&](int poses, int block, int chunks) {
-        const auto k = std::make_tuple(kind, padded, ctx->moving ? 1 : 0, poses, ctx->n_points);
-        if (block)
-            ctx->tuned[k] = {block, chunks};
-        else
-            ctx->tuned.erase(k);
+        ctx->tuned[std::make_tuple(kind, padded, ctx->moving ? 1 : 0, poses, ctx->n_points)] = {block, chunks};
     };
-    tune(npose, 0, 0);  // time without an earlier entry
-    tune(A.T, 0, 0);
     const int blocks[] = {64, 128, 256};
     const int chunk_counts[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 13, 16, 20, 24, 32, 40, 48, 64, 96, 128};
-    std::vector<std::pair<int, int>> cand{{0, 0}};  // the default shape
+    // the default shape first (the search's own rule has block 64)
+    std::vector<std::pair<int, int>> cand{{64, 1}};
+    if (dmin_every(padded, ctx->n_points, npose, ctx->moving)) {
+        int chunk;
+        choose_tiles(kind, padded, npose, ctx->n_points, cand[0].first, cand[0].second, chunk);
+    }
     // chunk counts that the pass can take: ranges of the hierarchy, or (every
     // point) chunks of at least 32 points, 8 when there are few poses (the pass
     // then needs the point chunks to fill the chip)
@@ -684,7 +682,7 @@ int mppi_autotune(mppi_ctx ctx, const mppi_params* prm, int reps, int* out_block
             best[ci] = std::min(best[ci], ms / reps);
         }
     }
-    int best_b = 0, best_c = 0;
+    int best_b = cand[0].first, best_c = cand[0].second;
     float best_ms = 1e30f;
     for (size_t ci = 0; ci < cand.size(); ++ci)
         if (best[ci] < best_ms) {
@@ -728,14 +726,14 @@ int mppi_autotune(mppi_ctx ctx, const mppi_params* prm, int reps, int* out_block
             size_t bi = 0;
             for (size_t ci = 1; ci < vc.size(); ++ci)
                 if (vbest[ci] < vbest[bi]) bi = ci;
-            tune(A.T, dmin_every(padded, ctx->n_points, A.T, ctx->moving) || vc[bi] > 1 ? 64 : 0, vc[bi]);
+            tune(A.T, 64, vc[bi]);
         }
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (rc) return rc;
-    if (out_block) *out_block = best_b ? best_b : 64;
-    if (out_nchunk) *out_nchunk = std::max(best_c, 1);
+    if (out_block) *out_block = best_b;
+    if (out_nchunk) *out_nchunk = best_c;
     return MPPI_OK;
 }
 

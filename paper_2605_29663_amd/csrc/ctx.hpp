@@ -291,13 +291,13 @@ inline void choose_tiles(int kind, int padded, int npose, int n_points, int& blo
 // table; the registers allow 24 waves per compute unit (16 for polygons above
 // 32 vertices).  The poses are dealt so that one round of resident
 // workgroups takes them all: with a part of a second round, the chip waits
-// for few workgroups as long as for many.  block = poses per workgroup (0:
-// that rule).
+// for few workgroups as long as for many.  block = poses per workgroup; 0 and
+// 64, the smallest that can be asked for, stand for that rule.
 constexpr int DMIN_WAVES = emppi::SEARCH_WAVES;
 constexpr int DMIN_MAX_POSES = 16;  // per wave and tile
 inline void dmin_shape(int kind, int padded, int npose, int block, int& poses_per_wave, int& tiles) {
     const int waves = 256 * (kind == 0 && padded > 32 ? 16 : 24);
-    const int n = block ? block / DMIN_WAVES : std::max(1, (npose + waves - 1) / waves);
+    const int n = block > 64 ? block / DMIN_WAVES : std::max(1, (npose + waves - 1) / waves);
     tiles = (n + DMIN_MAX_POSES - 1) / DMIN_MAX_POSES;
     poses_per_wave = (n + tiles - 1) / tiles;
 }
