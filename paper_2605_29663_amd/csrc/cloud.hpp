@@ -6,7 +6,7 @@
 namespace emppi {
 
 constexpr int CLOUD_MAX_POINTS = 1 << 20;
-constexpr int CLOUD_BINS = 2048;         // ranges are binned by 16 octaves of 128
+constexpr int CLOUD_BINS = 2048;         // of the squared range (range_bin)
 constexpr int CLOUD_DENSE_MIN = 1 << 18;  // cells always held as a plain grid
 
 struct CloudArgs {
