@@ -131,8 +131,8 @@ MPPI_API int set_guidance(mppi_ctx ctx, const float* host_xy, int n);
  * host, may be NULL (non-NULL makes the call synchronous).  Deterministic.
  * Limits: 0 <= m <= MPPI_MAX_CLOUD, 0 <= n_out <= MPPI_MAX_CLOUD, voxel > 0,
  * r_max > 0, z_min <= z_max, all finite, and (max(|cx|, |cy|) + r_max) /
- * voxel < 2^29; otherwise MPPI_E_ARG.  Workspace: at most 32 to 64
- * bytes per input point (4 MB for small clouds), kept by the context.      */
+ * voxel < 2^29; otherwise MPPI_E_ARG.  Workspace, kept by the context: at
+ * most 57 bytes per input point, or 4 MB for small clouds.                 */
 #define MPPI_MAX_CLOUD (1 << 20)
 typedef struct mppi_cloud_params {
     float z_min, z_max, r_max, voxel;

@@ -163,7 +163,7 @@ int mppi_destroy(mppi_ctx ctx) {
                           &ctx->px, &ctx->py, &ctx->pvx, &ctx->pvy, &ctx->pidx, &ctx->n_valid,
                           &ctx->pxy, &ctx->leaf, &ctx->leaf_vel, &ctx->super, &ctx->points_ws,
                           &ctx->path, &ctx->cloud_keys, &ctx->cloud_first, &ctx->cloud_cell,
-                          &ctx->cloud_r2, &ctx->cloud_misc,
+                          &ctx->cloud_misc,
                           &ctx->eps_ws, &ctx->poses_ws, &ctx->jbase, &ctx->jt,
                           &ctx->key, &ctx->key64, &ctx->unew, &ctx->nom_poses,
                           &ctx->key_nom};

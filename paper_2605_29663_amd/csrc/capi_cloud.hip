@@ -68,15 +68,16 @@ int cloud_downsample(mppi_ctx ctx, const float* dxyz, int m, const float center[
         w.cells = w.nx * w.ny;
     }
     const size_t C = static_cast<size_t>(w.cells), words = (static_cast<size_t>(m) + 127) / 128 * 4;
-    if (w.nx == 0) HIP_TRY(ctx, ctx->cloud_keys.ensure(sizeof(unsigned long long) * C));
+    // the hash keys are done with when the ranges are written; at most m cells
+    // are occupied
+    HIP_TRY(ctx, ctx->cloud_keys.ensure((w.nx == 0 ? sizeof(unsigned long long) : sizeof(uint32_t)) * C));
     HIP_TRY(ctx, ctx->cloud_first.ensure(sizeof(int) * C));
-    HIP_TRY(ctx, ctx->cloud_cell.ensure(sizeof(uint2) * C));
-    HIP_TRY(ctx, ctx->cloud_r2.ensure(sizeof(uint32_t) * C));
+    HIP_TRY(ctx, ctx->cloud_cell.ensure(sizeof(uint2) * std::max<size_t>(std::min<size_t>(C, m), 1)));
     HIP_TRY(ctx, ctx->cloud_misc.ensure(sizeof(int) * (words + CLOUD_BINS + 8)));
     w.keys = ctx->cloud_keys.as<unsigned long long>();
     w.first = ctx->cloud_first.as<int>();
     w.cand = ctx->cloud_cell.as<uint2>();
-    w.key = ctx->cloud_r2.as<uint32_t>();
+    w.key = ctx->cloud_keys.as<uint32_t>();
     w.kept = ctx->cloud_misc.as<uint32_t>();
     w.hist = ctx->cloud_misc.as<int>() + words;
     w.state = w.hist + CLOUD_BINS;

@@ -23,11 +23,11 @@ struct CloudWork {
     unsigned long long* keys;  // nx == 0: the cells are a hash table's slots, these its keys (a power of two >= 2 m)
     int cells;
     int* first;                // cells: lowest point index of the voxel
-    uint32_t* key;             // cells: squared range bits of that point, or CLOUD_NONE
+    uint32_t* key;             // cells: squared range bits of that point, or CLOUD_NONE (in the keys' place)
     uint32_t* kept;            // one bit per point, a multiple of 4 words
     int* hist;                 // CLOUD_BINS: representatives per range bin
     int* state;                // 8 (CLOUD_*)
-    uint2* cand;               // cells: (range bits, point) of the bin that the budget cuts
+    uint2* cand;               // m at most: (range bits, point) of the bin that the budget cuts
 };
 enum { CLOUD_KEPT = 0, CLOUD_BIN = 1, CLOUD_NEED = 2, CLOUD_CAND = 3 };
 
