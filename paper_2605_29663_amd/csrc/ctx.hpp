@@ -199,7 +199,9 @@ inline int check_params(mppi_ctx ctx, const mppi_params* p) {
 
 inline StepArgs make_args(mppi_ctx ctx, const mppi_params* p, const float* q0, uint64_t seed,
                           uint64_t step) {
-    ctx->mid_tau = std::min(std::max(0.5f * p->dt * static_cast<float>(p->T), 0.0f), 100.0f);
+    // (mppi_rollout takes any dt)
+    const float mid = 0.5f * p->dt * static_cast<float>(p->T);
+    if (std::isfinite(mid)) ctx->mid_tau = std::min(std::max(mid, 0.0f), 100.0f);
     StepArgs a{};
     a.path = ctx->path.as<float2>();
     a.n_path = ctx->n_path;
