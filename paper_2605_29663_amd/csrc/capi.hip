@@ -59,12 +59,12 @@ void* scratch_ptr(int device) {
 
 namespace {
 
-// Head of the bound table (FootTable) of a footprint given as in
+// Head of the bound table (FootHead) of a footprint given as in
 // set_footprint: a grid of about FOOT_CELLS square cells over the bounding
 // box and a margin of a quarter of the footprint's mean size, which keeps
 // most of the points next to the footprint on the grid, where the bounds are
 // closest.
-FootTable foot_head(int kind, const float* host, int count) {
+FootHead foot_head(int kind, const float* host, int count) {
     const int w = kind == MPPI_FP_POLYGON ? 2 : 4;
     std::vector<double> v(host, host + static_cast<size_t>(w) * count);
     double lo[2] = {INFINITY, INFINITY}, hi[2] = {-INFINITY, -INFINITY}, reach = 0.0;
@@ -78,7 +78,7 @@ FootTable foot_head(int kind, const float* host, int count) {
     reach = std::hypot(std::max(std::fabs(lo[0]), std::fabs(hi[0])), std::max(std::fabs(lo[1]), std::fabs(hi[1])));
     const double margin = 0.25 * std::sqrt(W * H) + 0.02 * (W + H);
     const double w0 = W + 2 * margin, h0 = H + 2 * margin;
-    FootTable F{};
+    FootHead F{};
     F.nx = std::max(8, std::min(FOOT_CELLS / 8, static_cast<int>(std::sqrt(FOOT_CELLS * w0 / h0))));
     F.ny = FOOT_CELLS / F.nx;
     const double dx = w0 / F.nx, dy = h0 / F.ny;
@@ -108,10 +108,9 @@ FootTable foot_head(int kind, const float* host, int count) {
 // The footprint's bound table on the device (the stream is idle: set_footprint
 // waits before it changes what earlier steps read).
 int upload_foot(mppi_ctx ctx, DevBuf& buf, int kind, const float* host, int count) {
-    const FootTable F = foot_head(kind, host, count);
+    static_assert(MPPI_MAX_B == FOOT_EDGES && MPPI_MAX_R == FOOT_BOXES && 4 * FOOT_BOXES <= 256, "the kernel's LDS");
     HIP_TRY(ctx, buf.ensure(foot_table_bytes()));
-    HIP_TRY(ctx, hipMemcpy(buf.p, &F, offsetof(FootTable, far), hipMemcpyHostToDevice));
-    HIP_TRY(ctx, launch_foot_table(kind, buf.as<FootTable>(),
+    HIP_TRY(ctx, launch_foot_table(kind, foot_head(kind, host, count), buf.as<FootTable>(),
                                    kind == 0 ? ctx->poly_tab_a.as<float4>() : ctx->rects.as<float4>(),
                                    kind == 0 ? ctx->poly_tab_b.as<float4>() : nullptr,
                                    kind == 0 ? ctx->poly_verts.as<float2>() : nullptr, count, ctx->stream));

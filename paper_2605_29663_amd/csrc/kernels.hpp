@@ -99,7 +99,7 @@ hipError_t launch_points(const float* x, const float* y, const float* vx, const 
 // reaches at most v . u + eps, where v is one of its corners, so the distance
 // of a point b at |b| u lies in [|b| - v . u - eps, |b - v|].
 constexpr int FAR_BINS = 64;
-struct FootTable {
+struct FootHead {
     float cx, cy;      // centre of the bounding box
     float radius;      // of a circle around (cx, cy) that holds the footprint
     float centre_d;    // signed distance at (cx, cy), rounded up
@@ -110,16 +110,18 @@ struct FootTable {
     float base, quantum, err_cell, err_linear;
     int nx, ny;
     int pad_[15];
+};
+struct FootTable : FootHead {
     float4 far[FAR_BINS];  // v (from the centre), eps, unused
 };
 static_assert(sizeof(FootTable) == 128 + 16 * FAR_BINS, "the cells start on 128 bytes of the buffer");
 constexpr int FOOT_CELLS = 4096;  // most cells of a table (16 KB of LDS)
 inline size_t foot_table_bytes() { return sizeof(FootTable) + sizeof(uint32_t) * FOOT_CELLS; }
-// Fill the cells and far[] of the table at `table` (its head is already there) from
-// the point-wise tables of the footprint (launch_sdf_points) and a polygon's
-// vertices.
-hipError_t launch_foot_table(int kind, FootTable* table, const float4* tab_a, const float4* tab_b,
-                             const float2* verts, int count, hipStream_t s);
+constexpr int FOOT_EDGES = 64, FOOT_BOXES = 32;  // most edges of a polygon, boxes of a cover
+// Fill the table at `table`, from its head, the point-wise tables of the
+// footprint (launch_sdf_points) and a polygon's vertices.
+hipError_t launch_foot_table(int kind, const FootHead& head, FootTable* table, const float4* tab_a,
+                             const float4* tab_b, const float2* verts, int count, hipStream_t s);
 
 // Time of pose g for moving points: h = (g / div) % mod, t = (h + off) dt.
 struct PoseTime {

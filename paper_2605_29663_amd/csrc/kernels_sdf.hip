@@ -30,29 +30,24 @@ __device__ __forceinline__ float2 far_dir(float a) {
     return make_float2(x * r, y * r);
 }
 
-// FootTable::far[k] from the polygon's vertices or the boxes: v reaches furthest in the bin's middle; eps is the most that
+// FootTable::far[k] from the footprint's corners: v reaches furthest in the bin's middle; eps is the most that
 // another corner reaches beyond it in the bin, widened for the rounding of
 // far_bin.  w . u is a cosine of u's angle: over the bin it is largest at an
 // end, or |w| if w's direction is inside.
-__device__ float4 far_entry(int kind, const FootTable& F, int k, const float2* __restrict__ verts,
-                            const float4* __restrict__ rects, int count) {
+__device__ float4 far_entry(const FootHead& F, int k, const float2* corner, int n) {
     constexpr float STEP = 4.0f / FAR_BINS;
     const float2 m = far_dir((k + 0.5f) * STEP - 1.0f), e0 = far_dir((k - 0.01f) * STEP - 1.0f),
                  e1 = far_dir((k + 1.01f) * STEP - 1.0f);
-    auto corner = [&](int i) {
-        if (kind == 0) return make_float2(verts[i].x - F.cx, verts[i].y - F.cy);
-        const float4 a = rects[i >> 2];
-        return make_float2(a.x + (i & 1 ? a.z : -a.z) - F.cx, a.y + (i & 2 ? a.w : -a.w) - F.cy);
-    };
-    const int n = kind == 0 ? count : 4 * count;
-    float2 v = corner(0);
+    float2 v = corner[0];
+#pragma unroll 4
     for (int i = 1; i < n; ++i) {
-        const float2 w = corner(i);
+        const float2 w = corner[i];
         if (w.x * m.x + w.y * m.y > v.x * m.x + v.y * m.y) v = w;
     }
     float eps = 0.0f;
+#pragma unroll 4
     for (int i = 0; i < n; ++i) {
-        float2 w = corner(i);
+        float2 w = corner[i];
         w.x -= v.x;
         w.y -= v.y;
         eps = fmaxf(eps, fmaxf(w.x * e0.x + w.y * e0.y, w.x * e1.x + w.y * e1.y));
@@ -75,29 +70,49 @@ __device__ float4 far_entry(int kind, const FootTable& F, int k, const float2* _
 //   - any other.
 // The second kind takes the search from 94 to 75 us a launch on average at 8192
 // corridor points and 16 vertices (the fill itself is a set-up cost).
-__global__ __launch_bounds__(256) void k_foot_table(int kind, const FootTable* __restrict__ F,
-                                                    uint32_t* __restrict__ cells, float4* __restrict__ far,
-                                                    const float4* __restrict__ ta,
-                                                    const float4* __restrict__ tb,
+__global__ __launch_bounds__(256) void k_foot_table(int kind, FootHead F, FootTable* __restrict__ table,
+                                                    const float4* __restrict__ tab_a,
+                                                    const float4* __restrict__ tab_b,
                                                     const float2* __restrict__ verts, int count) {
+    // the footprint in LDS: a cell's loops are chains of its loads
+    __shared__ float4 ta[FOOT_EDGES];
+    __shared__ float2 tb[FOOT_EDGES], corner[4 * FOOT_BOXES];
+    const int t = threadIdx.x;
+    if (t < count) {
+        ta[t] = tab_a[t];
+        if (kind == 0) tb[t] = make_float2(tab_b[t].x, tab_b[t].y);
+    }
+    __syncthreads();
     if (blockIdx.x == FOOT_CELLS / 256) {
-        if (threadIdx.x < FAR_BINS) far[threadIdx.x] = far_entry(kind, *F, static_cast<int>(threadIdx.x), verts, ta, count);
+        const int n = kind == 0 ? count : 4 * count;
+        if (t < n) {
+            if (kind == 0) {
+                corner[t] = make_float2(verts[t].x - F.cx, verts[t].y - F.cy);
+            } else {
+                const float4 a = ta[t >> 2];
+                corner[t] = make_float2(a.x + (t & 1 ? a.z : -a.z) - F.cx, a.y + (t & 2 ? a.w : -a.w) - F.cy);
+            }
+        }
+        __syncthreads();
+        if (t == 0) *static_cast<FootHead*>(table) = F;
+        if (t < FAR_BINS) table->far[t] = far_entry(F, t, corner, n);
         return;
     }
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= F->nx * F->ny) return;
-    const float x = (static_cast<float>(c % F->nx) + 0.5f - F->ox) * F->dx;
-    const float y = (static_cast<float>(c / F->nx) + 0.5f - F->oy) * F->dy;
-    const float r = F->err_cell;
+    const int c = blockIdx.x * blockDim.x + t;
+    if (c >= F.nx * F.ny) return;
+    const float x = (static_cast<float>(c % F.nx) + 0.5f - F.ox) * F.dx;
+    const float y = (static_cast<float>(c / F.nx) + 0.5f - F.oy) * F.dy;
+    const float r = F.err_cell;
     float d = INFINITY, second = INFINITY;  // nearest and next distance
     float gx = 0.0f, gy = 0.0f;             // gradient
     bool linear = false, smooth = false;
-    const float tol = 1e-5f * F->reach;
+    const float tol = 1e-5f * F.reach;
     if (kind == 0) {
         float m2 = INFINITY, v = 0.0f, wx = 0.0f, wy = 0.0f;  // (wx, wy): from the nearest point
         bool odd = false, inside = false;
         EdgeEval last = edge_eval(x, y, tb[count - 1].y, ta[count - 1].x, ta[count - 1].y,
                                   ta[count - 1].z, ta[count - 1].w, tb[count - 1].x);
+#pragma unroll 2
         for (int k = 0; k < count; ++k) {
             const float4 a = ta[k];
             const float len = tb[k].x;
@@ -132,7 +147,8 @@ __global__ __launch_bounds__(256) void k_foot_table(int kind, const FootTable* _
             gx = wx / dist;
             gy = wy / dist;
             smooth = true;
-            for (int k = 0; k < count; ++k) {
+    #pragma unroll 2
+        for (int k = 0; k < count; ++k) {
                 const float4 a = ta[k];
                 const float len = tb[k].x;
                 const EdgeEval e = edge_eval(x, y, tb[k].y, a.x, a.y, a.z, a.w, len);
@@ -149,6 +165,7 @@ __global__ __launch_bounds__(256) void k_foot_table(int kind, const FootTable* _
             }
         }
     } else {
+#pragma unroll 2
         for (int k = 0; k < count; ++k) {
             const float4 b = ta[k];
             const float s = signed_sqrt(box_s(x, y, b));
@@ -179,7 +196,8 @@ __global__ __launch_bounds__(256) void k_foot_table(int kind, const FootTable* _
             gx /= d;
             gy /= d;
             smooth = true;
-            for (int k = 0; k < count; ++k) {
+    #pragma unroll 2
+        for (int k = 0; k < count; ++k) {
                 const float4 b = ta[k];
                 if (signed_sqrt(box_s(x, y, b)) > d + 2.0f * r) continue;
                 const float s0 = __builtin_fmaf(b.x - x, gx, (b.y - y) * gy) + d;
@@ -193,12 +211,13 @@ __global__ __launch_bounds__(256) void k_foot_table(int kind, const FootTable* _
         cls = 0.0f;
     } else if (smooth) {
         const float bend = r * r / (2.0f * (fabsf(d) - r)) * 1.0001f + tol;
-        cls = fminf(ceilf(bend / ((F->err_cell - F->err_linear) * (1.0f / 7.0f))), 7.0f);
+        cls = fminf(ceilf(bend / ((F.err_cell - F.err_linear) * (1.0f / 7.0f))), 7.0f);
     }
     if (cls == 7.0f) gx = gy = 0.0f;
-    const float v = 8.0f * fminf(fmaxf(floorf((d - F->base) / (8.0f * F->quantum)), 0.0f), 8191.0f) + cls;
+    const float v = 8.0f * fminf(fmaxf(floorf((d - F.base) / (8.0f * F.quantum)), 0.0f), 8191.0f) + cls;
     const int ix = static_cast<int>(rintf(gx * 127.0f)), iy = static_cast<int>(rintf(gy * 127.0f));
-    cells[c] = static_cast<uint32_t>(v) | (static_cast<uint32_t>(ix & 255) << 16) | (static_cast<uint32_t>(iy & 255) << 24);
+    reinterpret_cast<uint32_t*>(table + 1)[c] =
+        static_cast<uint32_t>(v) | (static_cast<uint32_t>(ix & 255) << 16) | (static_cast<uint32_t>(iy & 255) << 24);
 }
 
 __global__ void k_key_init(unsigned int* __restrict__ key, unsigned long long* __restrict__ key64,
@@ -339,10 +358,10 @@ hipError_t launch_sdf_points(int kind, const float* px, const float* py, int n,
     return hipGetLastError();
 }
 
-hipError_t launch_foot_table(int kind, FootTable* table, const float4* tab_a, const float4* tab_b,
-                             const float2* verts, int count, hipStream_t s) {
-    hipLaunchKernelGGL(k_foot_table, dim3(FOOT_CELLS / 256 + 1), dim3(256), 0, s, kind, table,
-                       reinterpret_cast<uint32_t*>(table + 1), table->far, tab_a, tab_b, verts, count);
+hipError_t launch_foot_table(int kind, const FootHead& head, FootTable* table, const float4* tab_a,
+                             const float4* tab_b, const float2* verts, int count, hipStream_t s) {
+    hipLaunchKernelGGL(k_foot_table, dim3(FOOT_CELLS / 256 + 1), dim3(256), 0, s, kind, head, table, tab_a, tab_b,
+                       verts, count);
     return hipGetLastError();
 }
 
