@@ -78,7 +78,7 @@ struct PointWork {
     uint2* cell_rank;     // this and the rest unless points_small
     unsigned* cells;
     int* block_sums;
-    float* grid;  // sampled range: lo and length in x, in y
+    float2* range;  // sampled ranges (lo, length)
 };
 size_t points_work_bytes(int n, bool moving);
 hipError_t points_setup();  // once per device, before the first launch_points

@@ -79,17 +79,15 @@ __device__ __forceinline__ bool point_moves(const PointIn& in, int i) {
     return (in.vx && in.vx[i] != 0.0f) || (in.vy && in.vy[i] != 0.0f);
 }
 
-// One coordinate's range from a 64-point sample (one wave, all lanes): the 1/16
-// and 15/16 quantiles of the valid samples (all of them where those are equal),
-// widened by 1/4 of their distance on both sides; returns (lo, length).  The
-// sample takes one point from each 1/64 of the set, at uneven places: sets
-// that alternate between sources (sensors, rings of a sweep) at a period that
-// divides n / 64 would show one of them only.
-__device__ float2 sample_range(const PointIn& in, const float* a) {
+// One coordinate's range from a 64-point sample (one wave, all lanes), one from
+// each 1/64 of the set, at even or uneven places: the 1/16 and 15/16 quantiles of
+// the valid samples (all of them where those are equal), widened by 1/4 of
+// their distance on both sides; returns (lo, length).
+__device__ float2 sample_range(const PointIn& in, const float* a, bool uneven) {
     const int lane = threadIdx.x & (WAVE - 1);
     const int part = in.n / WAVE;
     const int i = static_cast<int>(static_cast<long long>(lane) * in.n / WAVE) +
-                  static_cast<int>(((lane * 0x9E3779B1u >> 16) * static_cast<unsigned>(part)) >> 16);
+                  (uneven ? static_cast<int>(((lane * 0x9E3779B1u >> 16) * static_cast<unsigned>(part)) >> 16) : 0);
     const bool ok = in.n > 0 && point_ok(in, i);
     const float v = ok ? a[i] : INFINITY;
     const int count = __popcll(__ballot(ok));
@@ -112,11 +110,25 @@ __device__ float2 sample_range(const PointIn& in, const float* a) {
     return make_float2(lo - wide, (hi + wide) - (lo - wide));
 }
 
-// The grid of nx x ny cells over the sampled ranges.  Neither side of the range
+// The ranges of samples 0 and 1 (even places in x, y), 2 and 3 (uneven ones), to
+// the waves' slots.
+__device__ __forceinline__ void sample_ranges(const PointIn& in, float2* range) {
+    const int wid = threadIdx.x / WAVE;
+    if (wid >= 4) return;
+    const float2 r = sample_range(in, wid & 1 ? in.y : in.x, wid >= 2);
+    if ((threadIdx.x & (WAVE - 1)) == 0) range[wid] = r;
+}
+
+// The grid of nx x ny cells over the sampled ranges: the even sample's, unless
+// the uneven one shows more than twice as much.  (Sets that alternate between
+// sources, the sensors of a vehicle or the rings of a sweep, at a period that
+// divides n / 64 show one of them only at even places.)  Neither side of the range
 // is taken as less than 1/16 of the other: along a wall the points of a leaf
 // would otherwise be close across it and far apart along it (8192 points of a
 // straight wall 20 m away, 2 cm thick: leaves 0.5 m long).
-__device__ __forceinline__ Grid make_grid(float2 x, float2 y, int nx, int ny) {
+__device__ __forceinline__ Grid make_grid(const float2* range, int nx, int ny) {
+    const float2 x = range[2].y > 2.0f * range[0].y ? range[2] : range[0];
+    const float2 y = range[3].y > 2.0f * range[1].y ? range[3] : range[1];
     auto axis = [](float2 a, float least, int cells, float& lo, float& s) {
         const float span = fmaxf(a.y, least);
         lo = a.x - 0.5f * (span - a.y);
@@ -269,19 +281,16 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_points_small(PointIn in, Poin
     constexpr bool PLACE = PT <= 8;
     static_assert(PLACE || !MOVING, "velocities are held");
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ float2 range[2];
+    __shared__ float2 range[4];
     __shared__ int wsum[SMALL_THREADS / WAVE];
     const int t = threadIdx.x, lane = t & (WAVE - 1), wid = t / WAVE;
     const int ncell = 1 << cell_bits;
     unsigned* hist = reinterpret_cast<unsigned*>(smem);
     uint4* h4 = reinterpret_cast<uint4*>(hist);
     unsigned short* group = reinterpret_cast<unsigned short*>(hist + ncell / 2);
-    // the sample's range (waves 0 and 1) while the others clear the counts
+    // the samples' ranges (waves 0 to 3) while the others clear the counts
     const int grid_bits = MOVING ? cell_bits - 1 : cell_bits;
-    if (wid < 2) {
-        const float2 r = sample_range(in, wid == 0 ? in.x : in.y);
-        if (lane == 0) range[wid] = r;
-    }
+    sample_ranges(in, range);
     for (int c = t; c < ncell / 8; c += SMALL_THREADS) h4[c] = make_uint4(0, 0, 0, 0);
     // every load of a batch is issued before the first result is used
     constexpr int HV = MOVING ? PT : 1;  // velocities held
@@ -318,7 +327,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_points_small(PointIn in, Poin
         }
     }
     __syncthreads();
-    const Grid G = make_grid(range[0], range[1], 1 << ((grid_bits + 1) / 2), 1 << (grid_bits / 2));
+    const Grid G = make_grid(range, 1 << ((grid_bits + 1) / 2), 1 << (grid_bits / 2));
 #pragma unroll
     for (int k = 0; k < PT; ++k) {
         cr[k] = 0;
@@ -467,14 +476,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_points_small(PointIn in, Poin
 // Cell counts cleared; the sample's range (workgroup 0).
 __global__ __launch_bounds__(1024) void k_points_init(PointIn in, PointWork w) {
     for (int c = blockIdx.x * 1024 + threadIdx.x; c < (1 << LARGE_CELL_BITS); c += gridDim.x * 1024) w.cells[c] = 0;
-    if (blockIdx.x != 0) return;
-    const int wid = threadIdx.x / WAVE;
-    if (wid > 1) return;
-    const float2 r = sample_range(in, wid == 0 ? in.x : in.y);
-    if ((threadIdx.x & (WAVE - 1)) == 0) {
-        w.grid[2 * wid] = r.x;
-        w.grid[2 * wid + 1] = r.y;
-    }
+    if (blockIdx.x == 0) sample_ranges(in, w.range);
 }
 
 // Cell and rank of every valid point ((~0, ~0) for the others).
@@ -484,8 +486,7 @@ __global__ __launch_bounds__(256) void k_points_count(PointIn in, PointWork w, b
     uint2 cr = make_uint2(~0u, ~0u);
     if (point_ok(in, i)) {
         const int bits = moving ? LARGE_CELL_BITS - 1 : LARGE_CELL_BITS;
-        const Grid G = make_grid(make_float2(w.grid[0], w.grid[1]), make_float2(w.grid[2], w.grid[3]),
-                                 1 << ((bits + 1) / 2), 1 << (bits / 2));
+        const Grid G = make_grid(w.range, 1 << ((bits + 1) / 2), 1 << (bits / 2));
         cr.x = cell_of(G, LARGE_CELL_BITS, moving, moving && point_moves(in, i),
                        in.x[i] + (in.vx ? in.vx[i] * in.mid : 0.0f), in.y[i] + (in.vy ? in.vy[i] * in.mid : 0.0f));
         cr.y = atomicAdd(&w.cells[cr.x], 1u);
@@ -676,7 +677,7 @@ hipError_t launch_points(const float* x, const float* y, const float* vx, const 
     p += sizeof(unsigned) * (1 << LARGE_CELL_BITS);
     w.block_sums = reinterpret_cast<int*>(p);
     p += sizeof(int) * 256;
-    w.grid = reinterpret_cast<float*>(p);
+    w.range = reinterpret_cast<float2*>((reinterpret_cast<uintptr_t>(p) + 7) & ~static_cast<uintptr_t>(7));
     const dim3 g((n + 255) / 256), b(256);
     hipLaunchKernelGGL(k_points_init, dim3(64), dim3(1024), 0, s, in, w);
     hipLaunchKernelGGL(k_points_count, g, b, 0, s, in, w, moving);
