@@ -319,7 +319,7 @@ int set_points(mppi_ctx ctx, const float* dx, const float* dy, const float* dvx,
     HIP_TRY(ctx, ctx->pxy.ensure(cap * (moving ? sizeof(float4) : sizeof(float2))));
     HIP_TRY(ctx, ctx->leaf.ensure(leaves * sizeof(float4)));
     HIP_TRY(ctx, ctx->super.ensure((leaves + SUPER_LEAVES - 1) / SUPER_LEAVES * sizeof(float4)));
-    HIP_TRY(ctx, ctx->points_ws.ensure(points_work_bytes(n, moving)));
+    HIP_TRY(ctx, ctx->points_ws.ensure(points_work_bytes(n)));
     if (moving) {
         HIP_TRY(ctx, ctx->pvx.ensure(cap * sizeof(float)));
         HIP_TRY(ctx, ctx->pvy.ensure(cap * sizeof(float)));

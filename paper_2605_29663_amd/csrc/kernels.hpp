@@ -17,13 +17,7 @@ constexpr int SUPER_LEAVES = 64;
 // batches, about as many as the hierarchy's tests and the points they leave,
 // and the order costs set_points 4 us.
 constexpr int POINTS_DIRECT_MAX = 512;
-// Sets prepared by one workgroup.  Many workgroups (7 launches, 24 - 26 us
-// whatever the size) are the shorter way for moving sets above 8 points a
-// thread, whose velocities it would read twice (20000 points 35 us by one
-// workgroup, 25 by many); static ones take 21 - 30 us by one, and a cycle of
-// 8193 points 131 us against 141.
-constexpr int POINTS_SMALL_MAX = 1 << 15, POINTS_SMALL_MAX_MOVING = 1 << 13;
-inline bool points_small(int n, bool moving) { return n <= (moving ? POINTS_SMALL_MAX_MOVING : POINTS_SMALL_MAX); }
+constexpr int POINTS_SMALL_MAX = 1 << 15;  // sets prepared by one workgroup
 constexpr int MPPI_MAX_T_DEV = 128;  // horizon capacity (MPPI_MAX_T of the C ABI)
 // Per-step result record: u*_0, u*_1, u*_2, valid, J_nom (noise-free cost of
 // the validated nominal), then padding.
@@ -75,12 +69,12 @@ struct PointSet {
 // Workspace of the many-workgroup preparation.
 struct PointWork {
     unsigned* positions;  // output position per point, ~0 if masked (above 8192 points)
-    uint2* cell_rank;     // this and the rest unless points_small
+    uint2* cell_rank;     // this and the rest above POINTS_SMALL_MAX
     unsigned* cells;
     int* block_sums;
     float2* range;  // sampled ranges (lo, length)
 };
-size_t points_work_bytes(int n, bool moving);
+size_t points_work_bytes(int n);
 hipError_t points_setup();  // once per device, before the first launch_points
 hipError_t launch_points(const float* x, const float* y, const float* vx, const float* vy,
                          const unsigned char* valid, int n, float mid, const PointSet& out, void* work, hipStream_t s);

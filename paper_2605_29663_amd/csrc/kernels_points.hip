@@ -10,10 +10,10 @@
 // one cell keep no particular order: the distance pass takes exact minima,
 // which do not depend on it, and every point carries the caller's index.
 //
-// Up to POINTS_SMALL_MAX points (moving: POINTS_SMALL_MAX_MOVING) one workgroup
-// sorts in LDS: the point arrays are a few hundred KB, so the pass is a chain of
-// memory and barrier latencies, and one launch is shorter than the seven of the
-// multi-workgroup path that larger sets take.
+// Up to POINTS_SMALL_MAX points one workgroup sorts in LDS: the point arrays
+// are a few hundred KB, so the pass is a chain of memory and barrier
+// latencies, and one launch is shorter than the five that a grid needs.
+// Larger sets take the multi-workgroup path.
 #include "kernels.hpp"
 #include "wave_ops.hpp"
 
@@ -279,7 +279,6 @@ template <int PT, bool MOVING>
 __global__ __launch_bounds__(SMALL_THREADS) void k_points_small(PointIn in, PointSet out, int cell_bits,
                                                                 unsigned* __restrict__ positions) {
     constexpr bool PLACE = PT <= 8;
-    static_assert(PLACE || !MOVING, "velocities are held");
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ float2 range[4];
     __shared__ int wsum[SMALL_THREADS / WAVE];
@@ -293,7 +292,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_points_small(PointIn in, Poin
     sample_ranges(in, range);
     for (int c = t; c < ncell / 8; c += SMALL_THREADS) h4[c] = make_uint4(0, 0, 0, 0);
     // every load of a batch is issued before the first result is used
-    constexpr int HV = MOVING ? PT : 1;  // velocities held
+    constexpr int HV = MOVING && PLACE ? PT : 1;  // velocities held
     constexpr int BATCH = PT < 8 ? PT : 8;
     float px[PT], py[PT], pvx[HV], pvy[HV];
     unsigned cr[PT];  // cell << 16 | rank within the cell; later the output position
@@ -320,9 +319,13 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_points_small(PointIn in, Poin
                             (!MOVING || (isfinite(vx[b]) && isfinite(vy[b])));
             okm |= ok ? 1u << k : 0u;
             if (MOVING) mvm |= vx[b] != 0.0f || vy[b] != 0.0f ? 1u << k : 0u;
-            if (MOVING) {
+            if (HV == PT) {
                 pvx[k % HV] = vx[b];
                 pvy[k % HV] = vy[b];
+            }
+            if (MOVING && !PLACE) {  // the positions are only sorted by
+                px[k] += vx[b] * in.mid;
+                py[k] += vy[b] * in.mid;
             }
         }
     }
@@ -332,8 +335,8 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_points_small(PointIn in, Poin
     for (int k = 0; k < PT; ++k) {
         cr[k] = 0;
         if (okm >> k & 1) {
-            const unsigned c = cell_of(G, cell_bits, MOVING, mvm >> k & 1, MOVING ? px[k] + pvx[k % HV] * in.mid : px[k],
-                                       MOVING ? py[k] + pvy[k % HV] * in.mid : py[k]);
+            const unsigned c = cell_of(G, cell_bits, MOVING, mvm >> k & 1, HV == PT ? px[k] + pvx[k % HV] * in.mid : px[k],
+                                       HV == PT ? py[k] + pvy[k % HV] * in.mid : py[k]);
             const unsigned sh = (c & 1) * 16;
             cr[k] = (c << 16) | ((atomicAdd(&hist[c >> 1], 1u << sh) >> sh) & 0xFFFFu);
         }
@@ -625,10 +628,8 @@ template <bool MOVING>
 hipError_t launch_small_m(const PointIn& in, const PointSet& out, unsigned* positions, hipStream_t s) {
     const int pt = (in.n + SMALL_THREADS - 1) / SMALL_THREADS;
     if (pt <= 4) return launch_small<4, MOVING>(in, out, positions, s);
-    if constexpr (MOVING)
-        return launch_small<8, true>(in, out, positions, s);
-    else
-        return pt <= 8 ? launch_small<8, false>(in, out, positions, s) : launch_small<32, false>(in, out, positions, s);
+    if (pt <= 8) return launch_small<8, MOVING>(in, out, positions, s);
+    return launch_small<32, MOVING>(in, out, positions, s);
 }
 
 }  // namespace
@@ -640,7 +641,8 @@ hipError_t points_setup() {
                        reinterpret_cast<const void*>(k_points_small<8, false>),
                        reinterpret_cast<const void*>(k_points_small<32, false>),
                        reinterpret_cast<const void*>(k_points_small<4, true>),
-                       reinterpret_cast<const void*>(k_points_small<8, true>)};
+                       reinterpret_cast<const void*>(k_points_small<8, true>),
+                       reinterpret_cast<const void*>(k_points_small<32, true>)};
     for (const void* f : k) {
         const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 152 * 1024);
         if (e != hipSuccess) return e;
@@ -648,10 +650,10 @@ hipError_t points_setup() {
     return hipSuccess;
 }
 
-size_t points_work_bytes(int n, bool moving) {
+size_t points_work_bytes(int n) {
     if (n <= 8 * SMALL_THREADS) return 0;
     const size_t positions = sizeof(unsigned) * static_cast<size_t>(n);
-    if (points_small(n, moving)) return positions;
+    if (n <= POINTS_SMALL_MAX) return positions;
     return positions + sizeof(uint2) * static_cast<size_t>(n) + sizeof(unsigned) * (1 << LARGE_CELL_BITS) +
            sizeof(int) * 256 + sizeof(float) * 64;
 }
@@ -667,10 +669,9 @@ hipError_t launch_points(const float* x, const float* y, const float* vx, const 
     PointWork w;
     char* p = static_cast<char*>(work);
     w.cell_rank = reinterpret_cast<uint2*>(p);  // first: 8-byte aligned
-    const bool small = points_small(n, moving);
-    if (!small) p += sizeof(uint2) * static_cast<size_t>(n);
+    if (n > POINTS_SMALL_MAX) p += sizeof(uint2) * static_cast<size_t>(n);
     w.positions = reinterpret_cast<unsigned*>(p);
-    if (small)
+    if (n <= POINTS_SMALL_MAX)
         return moving ? launch_small_m<true>(in, out, w.positions, s) : launch_small_m<false>(in, out, w.positions, s);
     p += sizeof(unsigned) * static_cast<size_t>(n);
     w.cells = reinterpret_cast<unsigned*>(p);
