@@ -163,21 +163,19 @@ struct PoseBounds {
     // anything, a rotation rounded to 16 bits for one).  The evaluators then see
     // the footprint scaled by k (SCALED: a polygon, whose vertices are turned by
     // (c, s)) or the points scaled by k (a cover): the table at (c, s) / k^2,
-    // its distances times k, or the table at (c, s).  Returns k, and the factor
-    // of distances between points in `apart`; without bounds (NaN) where k is no
-    // size to calculate with.
+    // its distances times k, or the table at (c, s), points k times as far apart.
+    // Without bounds (NaN) where k is no size to calculate with.
     template <bool SCALED>
-    __device__ __forceinline__ float init_scaled(const FootTable& F, float c, float s, float& apart) {
+    __device__ __forceinline__ void rescale(float c, float s, float& pslack, float& apart) {
         const float k2 = __builtin_fmaf(c, c, s * s);
-        apart = 1.0f;
-        if (fabsf(k2 - 1.0f) <= ROTATION_TOL) {
-            init(F, c, s);
-            return 1.0f;
-        }
         const bool usable = k2 > 1e-6f && k2 < 1e6f;
-        const float k = usable ? __builtin_amdgcn_sqrtf(k2) : 1.0f;
+        const float k = fabsf(k2 - 1.0f) <= ROTATION_TOL ? 1.0f : usable ? __builtin_amdgcn_sqrtf(k2) : NAN;
         if (SCALED) {
-            init(F, c / k2, s / k2);
+            const float inv = k == 1.0f ? 1.0f : 1.0f / k2;
+            ax *= inv;
+            bx *= inv;
+            ay *= inv;
+            by *= inv;
             dx *= k;
             dy *= k;
             gdx *= k;
@@ -187,11 +185,10 @@ struct PoseBounds {
             err_step *= k;
             err_linear *= k;
         } else {
-            init(F, c, s);
+            base = k == k ? base : k;
             apart = wave_uniform(k);
         }
-        if (!usable) base = NAN;
-        return wave_uniform(fmaxf(k, 1.0f));
+        pslack *= wave_uniform(fmaxf(k, 1.0f));
     }
 
     __device__ __forceinline__ void operator()(const uint32_t* cells, float px, float py, float& lb,
@@ -254,7 +251,7 @@ constexpr int DPP_ROR1 = 0x121, DPP_ROR2 = 0x122, DPP_ROR4 = 0x124, DPP_ROR8 = 0
 template <int HB>
 struct EvalPoly {
     static constexpr int WAVES = HB <= 2 ? 6 : 4;  // per SIMD, without scratch in the loops
-    static constexpr bool SCALED = true;           // PoseBounds::init_scaled
+    static constexpr bool SCALED = true;           // PoseBounds::rescale
     static constexpr bool EACH = false;            // has each()
     PolyPart<HB, EVAL_LANES> F;
     __device__ __forceinline__ void init(const float2* verts, const float4*, int n, int part, float4 q) {
@@ -569,10 +566,8 @@ __device__ __forceinline__ void cull_block(const CullArgs& A, const float2* __re
                             q = wave_uniform(Wv.pose[p]);
                             tau = MOVING ? wave_uniform(Wv.tau[p]) : 0.0f;
                             pslack = slack + (MOVING ? 2e-6f * (fabsf(q.x) + fabsf(q.y)) : 0.0f);
-                            if (__builtin_expect(scaled, 0))
-                                pslack *= B.init_scaled<Eval::SCALED>(F, q.z, q.w, apart);
-                            else
-                                B.init(F, q.z, q.w);
+                            B.init(F, q.z, q.w);
+                            if (__builtin_expect(scaled, 0)) B.template rescale<Eval::SCALED>(q.z, q.w, pslack, apart);
                             nkeep = 0;
                             c0 = 0;
                             nq0 = nq;
