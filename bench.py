@@ -28,7 +28,6 @@ from __future__ import annotations
 
 import argparse
 import ctypes
-import hashlib
 import json
 import math
 import os
@@ -98,7 +97,7 @@ def parse():
                          "the batch timed for it (c4, twice this many)")
     ap.add_argument("--graph", action="store_true",
                     help="time steps replayed from a captured graph of a one-scene batch "
-                         "(autotuned persistent distance kernel, timed on as many eager steps "
+                         "(with the batch autotuner's plan; the distance pass timed on as many eager steps "
                          "of the same batch right after)")
     ap.add_argument("--polygon-vertices", type=int, default=0,
                     help="c1/c2: replace the footprint by a seeded star-shaped polygon of this "
@@ -118,11 +117,6 @@ def padded_count(kind, count):
     return next(b for b in (1, 2, 3, 4, 6, 8, 12, 16, 24, 32) if count <= b)
 
 
-KERNEL_SOURCES = [os.path.join(ROOT, "paper_2605_29663_amd", "csrc", f)
-                  for f in ("kernels_sdf.hip", "kernels_sdf_every.hip", "kernels_search_batch.hip", "kernels_batch.hip",
-                            "cull_device.hpp", "sdf_device.hpp", "wave_ops.hpp", "kernels.hpp")]
-
-
 def host_cpu_model():
     try:
         for line in open("/proc/cpuinfo"):
@@ -131,25 +125,6 @@ def host_cpu_model():
     except OSError:
         pass
     return None
-
-
-def kernel_sha256():
-    h = hashlib.sha256()
-    for f in KERNEL_SOURCES:
-        h.update(open(f, "rb").read())
-    return h.hexdigest()
-
-
-def traffic_record(workload):
-    """HBM bytes per launch measured by rocprofv3 counters, if they were taken on
-    the current source of the distance kernels (sha256 recorded with the numbers)."""
-    path = os.path.join(ROOT, "profiles", f"dmin_{workload}_traffic.json")
-    if not os.path.exists(path):
-        return None
-    rec = json.load(open(path))
-    if rec.get("kernel_sha256") != kernel_sha256():
-        return None
-    return rec.get("bytes_per_launch")
 
 
 def copy_probe(mib):
@@ -464,7 +439,7 @@ def run_batched(args):
                        "p95": float(np.percentile(lat, 95) * 1e3)},
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "f32",
         "data": "synthetic (seeded scene generator)",
-        "config": {"workload": "64 uneven scenes, batched persistent launch in a hipGraph",
+        "config": {"workload": "64 uneven scenes, one batched step in a hipGraph",
                    "scenes": n, "pairs_per_step": pairs_step,
                    "K": "512..4096", "T": "20..60", "N": "1e3..3e4", "B": "4..32",
                    "motion_model": "unicycle / ackermann"},
@@ -473,7 +448,7 @@ def run_batched(args):
                      "unit": "T VALU lane-instr/s", "frac": achieved / VALU_PEAK_TOPS,
                      "count": "11 per point-edge pair + 5 per pose-point pair, covered (not each evaluated)",
                      "frac_kernel_count": achieved_kernel / VALU_PEAK_TOPS,
-                     "traffic": traffic_record("c4"), "kernel_ms": k_avg, "launches": k_n,
+                     "kernel_ms": k_avg, "launches": k_n,
                      "timing": "HIP events around the distance launches of eager steps",
                      "tiles": {"pairs_per_item": work, "items_main": items_main,
                                "items_validation": items_val, "source": "batch autotuner"}},
@@ -646,7 +621,6 @@ def main():
     k_avg_ms = k_ms / max(k_n, 1)
     achieved = ops_launch / (k_avg_ms / 1e3) / 1e12
     achieved_kernel = ops_kernel / (k_avg_ms / 1e3) / 1e12
-    workload = args.config
 
     out = {
         "metric": "SDF evals/s (K*T*N*edges per MPPI step) and MPPI step latency",
@@ -671,14 +645,12 @@ def main():
                    "motion_model": prm["model"], "dt": prm["dt"]},
         "roofline": {"bound": "alu",
                      "kernel": ("distance pass of a one-scene batch" if args.graph else
-                                "every point (at most 512)" if N <= 512 else "k_dmin (bounded search)"),
+                                "every point" if N <= 512 else "k_dmin (bounded search)"),
                      "achieved": achieved, "peak": VALU_PEAK_TOPS,
                      "unit": "T VALU lane-instr/s", "frac": achieved / VALU_PEAK_TOPS,
                      "count": f"11 per point-{'edge' if kind == 0 else 'box'} pair + "
                               f"{5 + (1 if moving else 0)} per pose-point pair, covered (not each evaluated)",
                      "frac_kernel_count": achieved_kernel / VALU_PEAK_TOPS,
-                     "traffic": (None if args.graph or args.polygon_vertices else
-                                 traffic_record(workload)),
                      "kernel_ms": k_avg_ms, "launches": k_n,
                      "timing": "HIP events around every distance launch of as many steps right after "
                                "the timed region (%.4f ms per step with the events)" % ms_step_events,

@@ -96,8 +96,8 @@ typedef struct mppi_params {
 /* Graph mode (enable != 0): mppi_step calls without diagnostics (diag NULL)
  * replay a captured hipGraph of the whole step (a one-scene batch of this
  * context, see mppi_batch_create: bit-identical results, fewer launch
- * overheads, the persistent distance kernel).  The first step of a
- * parameter set builds the batch and autotunes its item size
+ * overheads).  The first step of a parameter set builds the batch and
+ * autotunes its item size
  * (mppi_batch_autotune: about 80 launches of the distance pass); the graph
  * is rebuilt when the parameters change and re-planned when points or
  * footprint change.  With profiling on (mppi_set_profiling) the batch runs
@@ -338,9 +338,10 @@ MPPI_API int mppi_get_profile(mppi_ctx ctx, double* ms, long long* launches);
  * Batched step: many independent scenes of uneven size in one launch
  * sequence.  Each scene is an existing context (its footprint and point set)
  * plus its own mppi_params (model, K, T, costs may all differ).  The
- * signed-distance stage of all scenes runs as one persistent kernel per
- * register class pulling (scene, pose tile, point chunk) items from a
- * longest-first queue; the whole cycle can be captured in one hipGraph and
+ * signed-distance stage of all scenes runs as one launch per evaluator over
+ * (scene, poses) items, longest first, and for scenes of few points as one
+ * persistent kernel per register class pulling (scene, pose tile, point chunk)
+ * items from a queue; the whole cycle can be captured in one hipGraph and
  * replayed.  Each scene's outputs are bit-identical to mppi_step on that
  * scene's context with the same arguments.
  * ------------------------------------------------------------------------ */

@@ -48,7 +48,7 @@ int cloud_downsample(mppi_ctx ctx, const float* dxyz, int m, const float center[
     int cap = 256;
     while (cap < 2 * m) cap <<= 1;
     // The voxels of the range as a plain grid when they are no more than the
-    // hash table's slots or CLOUD_DENSE_MIN: 2^20 points take 56 us with a
+    // hash table's slots or CLOUD_DENSE_MIN: 2^20 points take 59 us with a
     // grid of 40000 cells and 83 with one of 10^6, hashed 85 and 102; 3000
     // points with 160000 cells 39 and hashed 41, with 4 10^6 cells 54 and
     // hashed 43.  The margins cover the rounding of the range test (relative 1e-6 of r_max) and of the

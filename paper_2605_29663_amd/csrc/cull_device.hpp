@@ -25,15 +25,16 @@
 //      (the same operations on the same operands, hence the same bits, as an
 //      evaluation of every point by one lane); many points of one pose go one
 //      per lane where the footprint is boxes.
-// It is bound by the latency of the short dependent phases of step 2, hence
+// It is bound by issue, about 800 vector instructions a pose at 39 to 54 % of the
+// peak rate, and by the latency of the short dependent phases of step 2, hence
 // many waves with few poses each, LDS for everything that is read at random
 // and one pass over memory for the points.  Measured against evaluating every
 // point (which ran at 86 - 92 % of the VALU issue rate): 81920 poses, 8192
 // corridor points, 16 vertices 1800 -> 135 us; 204800 poses, 20000 points of
 // which 30 % move, 4 boxes 2700 -> 500 us.  Sets that the bounds cannot thin out
 // cost more than every point would: 20480 poses against 8192 points, with 16
-// edges / 4 boxes, a field 60 / 57 us, a wall 20 m away 350 / 325, a ring of 5 m
-// 640 / 340, all in one place 2740 / 815, every point evaluated 510 - 620 / 122
+// edges / 4 boxes, a field 60 / 57 us, a wall 20 m away 370 / 325, a ring of 5 m
+// 640 / 365, all in one place 2740 / 815, every point evaluated 510 - 620 / 122
 // (before FootTable::far: wall 2300 / 1760, ring 2430 / 2010).
 #pragma once
 #include "sdf_device.hpp"

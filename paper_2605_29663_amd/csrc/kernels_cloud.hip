@@ -14,7 +14,7 @@
 // representatives' ranges and an exact selection within one bin, and the kept
 // points' bits, one per input point, give the input order by population
 // counts.  What bounds it is the chain of six small launches.  2^20 points in
-// 24 x 24 m, range 10 m, voxel 0.1 m, budget 8192: 116 -> 64 us with the call's overhead, 38 of them in
+// 24 x 24 m, range 10 m, voxel 0.1 m, budget 8192: 116 -> 59 us with the call's overhead, 38 of them in
 // the kernels (insertion 19), against nine launches with a hash insertion of
 // 24 us and four histograms and a three-level scan over all the points.
 #include <algorithm>
