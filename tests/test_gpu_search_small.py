@@ -47,27 +47,30 @@ def test_rule_changes_no_result(n, prims, poses, moving):
     ctx.close()
 
 
-@pytest.mark.parametrize("K,T,N,prims,us", [(512, 16, 700, -2, 10.0), (256, 20, 1000, 4, 13.5), (64, 20, 600, 3, 9.5)])
-def test_small_steps_evaluate_every_point(K, T, N, prims, us):
-    """The distance pass of small steps (with its timing events about 9 / 11 / 7 us;
-    the search takes 15 / 16 / 12)."""
+@pytest.mark.parametrize("K,T,N,prims,factor", [(512, 16, 700, -2, 1.5), (256, 20, 1000, 4, 1.7), (64, 20, 600, 3, 1.5)])
+def test_small_steps_evaluate_every_point(K, T, N, prims, factor):
+    """The distance pass of small steps against that of 500 points, which are
+    evaluated point by point (with the timing events about 8 / 11 / 7 us against
+    8 / 8 / 6.5; searched, the larger sets take 15 / 16 / 12)."""
     import torch
     import paper_2605_29663_amd as pkg
     rng = np.random.default_rng(7)
     kind, geom = _footprint(rng, prims)
     ctx = pkg.Context(0)
     ctx.set_footprint(kind, geom)
-    x, y = rng.uniform(1.5, 3, (2, N)) * rng.choice([-1, 1], (2, N))
-    ctx.set_points(x.astype(np.float32), y.astype(np.float32))
+    x, y = (rng.uniform(1.5, 3, (2, N)) * rng.choice([-1, 1], (2, N))).astype(np.float32)
     prm = scenes.params("c1", K=K, T=T, footprint_kind=kind, validate=0)
     U = torch.zeros((T, 2), device="cuda")
-    best = np.inf
-    for _ in range(6):
-        ctx.mppi_set_profiling(True)
-        for _ in range(10):
-            ctx.mppi_step(prm, np.zeros(3, np.float32), U, 1, 0)
-        ms, n = ctx.mppi_get_profile()
-        best = min(best, 1e3 * ms / n)
+    best = []
+    for n in (500, N):
+        ctx.set_points(x[:n], y[:n])
+        best.append(np.inf)
+        for _ in range(6):
+            ctx.mppi_set_profiling(True)
+            for _ in range(10):
+                ctx.mppi_step(prm, np.zeros(3, np.float32), U, 1, 0)
+            ms, launches = ctx.mppi_get_profile()
+            best[-1] = min(best[-1], 1e3 * ms / launches)
     print(best)
-    assert best < us
+    assert best[1] < factor * best[0], best
     ctx.close()
